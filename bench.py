@@ -63,7 +63,8 @@ def traffic_from_profile(kernel_prefix: str, tag: str):
     return float(t.group(1))
 
 
-KERNEL_SOURCES = ("csrc/eval.hip", "csrc/ops.h", "csrc/tables.h", "csrc/tables.cpp", "build.py")
+KERNEL_SOURCES = ("csrc/eval.hip", "csrc/near.hip", "csrc/pass.hip", "csrc/ops.h",
+                  "csrc/tables.h", "csrc/tables.cpp", "build.py")
 
 
 def kernel_source_hash() -> str:

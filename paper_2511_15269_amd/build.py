@@ -17,8 +17,13 @@ OUT = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libfmm.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["api.cpp", "tables.cpp", "sort.hip", "tree.hip", "lists.hip", "direct.hip", "eval.hip", "batch.hip",
-           "multi.hip", "noalloc.hip"]
+SOURCES = ["api.cpp", "tables.cpp", "sort.hip", "tree.hip", "lists.hip", "direct.hip", "near.hip",
+           "pass.hip", "batch_near.hip", "multi.hip", "noalloc.hip"]
+# compiled once per expansion order (-DFMM_ORDER=p), the longest units first
+PER_ORDER = ["eval.hip", "batch.hip"]
+ORDERS = range(1, 11)
+UNITS = [(src, p) for p in sorted(ORDERS, reverse=True) for src in PER_ORDER] + \
+        [(src, None) for src in SOURCES]
 
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-unused-function",
           "-I" + os.path.join(os.path.dirname(PKG), "include")]
@@ -30,9 +35,13 @@ DEVICE = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-pa
           "-mllvm", "-pragma-unroll-threshold=200000"]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(OUT, os.path.splitext(src)[0] + ".o")
+def _compile(unit) -> str:
+    src, order = unit
+    name = os.path.splitext(src)[0]
+    obj = os.path.join(OUT, name + (".o" if order is None else f"_p{order}.o"))
     cmd = [HIPCC] + COMMON
+    if order is not None:
+        cmd += [f"-DFMM_ORDER={order}"]
     if src.endswith(".hip"):
         cmd += DEVICE + ["-x", "hip"]
     else:
@@ -46,9 +55,9 @@ def _compile(src: str) -> str:
 
 def build(verbose: bool = False) -> str:
     os.makedirs(OUT, exist_ok=True)
-    workers = min(len(SOURCES), max(1, (os.cpu_count() or 4)))
+    workers = min(len(UNITS), max(1, (os.cpu_count() or 4)))
     with ThreadPoolExecutor(workers) as ex:
-        objs = list(ex.map(_compile, SOURCES))
+        objs = list(ex.map(_compile, UNITS))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp] + objs
     r = subprocess.run(cmd, capture_output=True, text=True)

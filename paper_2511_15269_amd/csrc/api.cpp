@@ -399,10 +399,6 @@ void build_structure(fmm_plan* pl, const double* pos, int64_t n, const fmm_param
   }
 }
 
-bool batched_plan(const fmm_plan* pl) {
-  return pl->prm.precision == FMM_FP32 && pl->prm.max_rhs > 1 && pl->nsides == 1;
-}
-
 // Evaluation workspace (one allocation, workspace_layout) and the batched
 // M2L partial rows, sized from the plan's counts.
 void alloc_workspace(fmm_plan* pl, hipStream_t st) {
@@ -449,6 +445,7 @@ fmm_status fmm_plan_create_ex(const double* pos, int64_t n, const fmm_params* pr
     use_allocator(pl.get(), allocator, st, flags);
     try {
       build_structure(pl.get(), pos, n, prm, st);
+      for (int d = 0; d < 2; ++d) make_work(pl.get(), d, st);
       make_steps(pl.get(), {{TreeDesc{pl->L, pl->level_off, 0, 0}}}, st);
       alloc_workspace(pl.get(), st);
       make_fork(pl.get());
@@ -564,6 +561,7 @@ fmm_status fmm_plan_create_st(const double* src, int64_t ns, const double* tgt, 
         pl->side[k].nleaf = sub[k]->nleaf;
       }
       build_lists(pl.get(), ts, tt, st);
+      for (int d = 0; d < 2; ++d) make_work(pl.get(), d, st);
       make_steps(pl.get(), {{ts}, {tt}}, st);
       (void)hipStreamSynchronize(st);
       free_subs();
@@ -605,7 +603,7 @@ fmm_status fmm_plan_get_info(const fmm_plan* pl, fmm_plan_info* info) {
     r.p2p_interactions = pl->p2p_inter;
     r.device_bytes = (int64_t)pl->device_bytes;
     r.workspace_bytes = (int64_t)pl->workspace_bytes;
-    r.p2p_items = pl->lists[0].n_pitems;
+    r.p2p_items = pl->lists[0].near.n;
     *info = r;
   });
 }

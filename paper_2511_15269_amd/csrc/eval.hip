@@ -32,9 +32,8 @@
 //             lanes; each leaf then adds its parent's shifted local.
 //   P2M:      block = leaf, thread = point, LDS reduction over points.
 //   L2P:      block = target leaf, thread = target point; writes outputs.
-//   P2P:      block = target leaf, thread = target point; adds the near
-//             field; the source points of the direct list are read with
-//             wave-uniform (scalar) loads.
+// The near field (P2P) is in near.hip.  This file is compiled once per
+// expansion order (FMM_ORDER), so that the orders' kernels build in parallel.
 #include <cmath>
 
 #include <type_traits>
@@ -242,9 +241,6 @@ __device__ __forceinline__ void turn_shared(T* v, bool act, const Turn<P, KIND, 
   __syncthreads();
   if (act) turn_back<P, KIND, T, DM>(v, g, tab);
 }
-
-// Waves per translation of the shared forms.
-constexpr int kShareWaves = 4;
 
 // ---------------------------------------------------------------- M2M
 template <int P, typename T>
@@ -641,256 +637,15 @@ __global__ __launch_bounds__(64) void k_l2p(
   }
 }
 
-// One source point against the lane's target at (xi, yi, zi): the
-// difference is taken in FP64 and rounded to T.  SAFE: pairs at distance 0
-// contribute nothing (needed within a leaf, and between leaves when the
-// point set has coincident points); otherwise the pair is known to be apart.
-template <typename T, bool FIELD, bool SAFE>
-__device__ __forceinline__ void p2p_pair(const Src<T>& s, double xi, double yi, double zi,
-                                         T& u, T& gx, T& gy, T& gz) {
-  const T dx = T(xi - s.x), dy = T(yi - s.y), dz = T(zi - s.z);
-  const T r2 = dx * dx + dy * dy + dz * dz;
-  const T inv0 = inv_sqrt(r2);
-  const T inv = SAFE ? (r2 > T(0) ? inv0 : T(0)) : inv0;
-  const T qi = s.q * inv;
-  u += qi;
-  if (FIELD) {
-    const T q3 = qi * inv * inv;
-    gx = fma(q3, dx, gx);
-    gy = fma(q3, dy, gy);
-    gz = fma(q3, dz, gz);
-  }
-}
-
-constexpr int kChunk = 8;
-
-// P2P: writes -1/(4 pi) sum q/r and the matching field over the direct list,
-// in leaf order (near[i] and near[n + 3 i + c]); L2P adds the far field and
-// writes the outputs in input order.
-// Block = one near-field work item (a run of a target leaf's direct list;
-// most leaves have one), lane = target point (position from the plan's
-// leaf-ordered coordinates; the sources' records are this pass's, written
-// by P2M).  A leaf's only item writes its near field; the items of a split
-// leaf write partial rows that k_p2p_sum adds in item order.  G source groups: lanes
-// [g*64/G, (g+1)*64/G) share targets with the other groups but walk every
-// G-th source point starting at point g.  G = 1 keeps all source reads
-// wave-uniform (scalar loads).  G = 2, 4 fill the wave when leaves hold at
-// most 32 or 16 points; each source leaf is then first copied into LDS with
-// one coalesced 16-byte load per lane, and the groups read their records
-// from there (a per-lane global read of every record would saturate the
-// texture address unit).  Per source leaf the partial sums are added to the
-// running sums with Neumaier compensation (FP32 form); group sums are then
-// combined with cross-lane shuffles in a fixed order.
-template <typename T, bool FIELD, int G>
-__global__ __launch_bounds__(64) void k_p2p(
-    int64_t n, const int32_t* __restrict__ item_leaf, const int32_t* __restrict__ item_kb,
-    const int32_t* __restrict__ item_ke, const int64_t* __restrict__ item_out,
-    const int32_t* __restrict__ leaf_start, const double* __restrict__ xs,
-    const double* __restrict__ ys, const double* __restrict__ zs,
-    const Src<T>* __restrict__ src, const int32_t* __restrict__ p2p_src, int dup,
-    T* __restrict__ near, T* __restrict__ part) {
-  constexpr int TL = 64 / G;  // targets per pass
-  constexpr bool kComp = sizeof(T) == 4;  // FP32: compensated sums
-  // G > 1: one source leaf (at most TL points) staged as 16-byte words
-  __shared__ __align__(32) double2 stage[G > 1 ? 2 * TL : 1];
-  // items in target-leaf order, handed to the XCDs in runs of 64:
-  // neighbouring target leaves share most source leaves, so their records
-  // stay in one XCD's L2, while leaves of unequal cost (several problems,
-  // clustered points) spread over all XCDs
-  const int item = (int)xcd_chunked<64>(blockIdx.x, gridDim.x);
-  const int leaf = item_leaf[item];
-  const int lane = threadIdx.x;
-  const int g = G == 1 ? 0 : lane / TL;
-  const int st = leaf_start[leaf], en = leaf_start[leaf + 1];
-  const int pb = item_kb[item], pe = item_ke[item];
-  const int64_t po = item_out[item];
-  for (int i0 = st; i0 < en; i0 += TL) {
-    const int i = i0 + lane % TL;
-    const bool live = i < en;
-    const int ia = live ? i : st;
-    const Src<T> a{xs[ia], ys[ia], zs[ia], T(0)};
-    T u = T(0), gx = T(0), gy = T(0), gz = T(0);
-    T cu = T(0), cgx = T(0), cgy = T(0), cgz = T(0);
-    for (int k = pb; k < pe; ++k) {
-      const int sl = p2p_src[k];
-      const int js = leaf_start[sl], cnt = leaf_start[sl + 1] - js;
-      T lu = T(0), lx = T(0), ly = T(0), lz = T(0);
-      const int full = cnt / G;  // points per group present in every group
-      // distance-0 guard only where it can matter: the target leaf itself,
-      // or every leaf when the point set has coincident points
-      const bool safe = dup || sl == leaf;
-      const Src<T>* rec;
-      int stride;
-      if (G == 1) {
-        rec = src + js;
-        stride = 1;
-      } else {
-        // cnt <= TL: the leaf's records are 2 cnt <= 64 words
-        const double2* words = reinterpret_cast<const double2*>(src + js);
-        __syncthreads();  // previous leaf's reads are done
-        if (lane < 2 * cnt) stage[lane] = words[lane];
-        __syncthreads();
-        rec = reinterpret_cast<const Src<T>*>(stage) + g;
-        stride = G;
-      }
-      auto sweep = [&](auto safe_tag) {
-        constexpr bool S = decltype(safe_tag)::value;
-        int c = 0;
-        for (; c + kChunk <= full; c += kChunk) {
-          Src<T> r[kChunk];
-#pragma unroll
-          for (int t = 0; t < kChunk; ++t) r[t] = rec[(c + t) * stride];
-#pragma unroll
-          for (int t = 0; t < kChunk; ++t)
-            p2p_pair<T, FIELD, S>(r[t], a.x, a.y, a.z, lu, lx, ly, lz);
-        }
-        for (; c < full; ++c) p2p_pair<T, FIELD, S>(rec[c * stride], a.x, a.y, a.z, lu, lx, ly, lz);
-        if (G > 1 && g < cnt - full * G)
-          p2p_pair<T, FIELD, S>(rec[full * G], a.x, a.y, a.z, lu, lx, ly, lz);
-      };
-      if (safe)
-        sweep(std::true_type{});
-      else
-        sweep(std::false_type{});
-      if (kComp) {
-        neumaier(u, cu, lu);
-        if (FIELD) {
-          neumaier(gx, cgx, lx);
-          neumaier(gy, cgy, ly);
-          neumaier(gz, cgz, lz);
-        }
-      } else {
-        u += lu;
-        gx += lx;
-        gy += ly;
-        gz += lz;
-      }
-    }
-    u += cu;
-    gx += cgx;
-    gy += cgy;
-    gz += cgz;
-#pragma unroll
-    for (int off = TL; off < 64; off <<= 1) {
-      u += __shfl_xor(u, off, 64);
-      if (FIELD) {
-        gx += __shfl_xor(gx, off, 64);
-        gy += __shfl_xor(gy, off, 64);
-        gz += __shfl_xor(gz, off, 64);
-      }
-    }
-    if (live && g == 0) {
-      // field = -grad u;  grad of the near part is +(1/4pi) sum q d/r^3
-      if (po < 0) {  // the leaf's only item: its near field
-        near[i] = -T(kInv4Pi) * u;
-        if (FIELD) {
-          T* f = near + n + 3 * (int64_t)i;
-          f[0] = -T(kInv4Pi) * gx;
-          f[1] = -T(kInv4Pi) * gy;
-          f[2] = -T(kInv4Pi) * gz;
-        }
-      } else {  // one of several items of the leaf: rows of its partial sums
-        const int nt = en - st, li = i - st;
-        T* r = part + po;
-        r[li] = -T(kInv4Pi) * u;
-        if (FIELD) {
-          r[nt + li] = -T(kInv4Pi) * gx;
-          r[2 * nt + li] = -T(kInv4Pi) * gy;
-          r[3 * nt + li] = -T(kInv4Pi) * gz;
-        }
-      }
-    }
-  }
-}
-
-// Near field of the leaves whose direct list was split into several items:
-// the items' partial rows added in item order (Neumaier-compensated in
-// FP32).  Block = split leaf, thread = target point.
-template <typename T, bool FIELD>
-__global__ __launch_bounds__(64) void k_p2p_sum(
-    int64_t n, const int32_t* __restrict__ split_leaf, const int32_t* __restrict__ split_first,
-    const int32_t* __restrict__ split_cnt, const int64_t* __restrict__ item_out,
-    const int32_t* __restrict__ leaf_start, const T* __restrict__ part, T* __restrict__ near) {
-  constexpr bool kComp = sizeof(T) == 4;
-  const int leaf = split_leaf[blockIdx.x];
-  const int f = split_first[blockIdx.x], c = split_cnt[blockIdx.x];
-  const int st = leaf_start[leaf], nt = leaf_start[leaf + 1] - st;
-  for (int li = threadIdx.x; li < nt; li += blockDim.x) {
-#pragma unroll
-    for (int comp = 0; comp < (FIELD ? 4 : 1); ++comp) {
-      T acc = T(0), cc = T(0);
-      for (int j = f; j < f + c; ++j) {
-        const T x = part[item_out[j] + (int64_t)comp * nt + li];
-        if (kComp)
-          neumaier(acc, cc, x);
-        else
-          acc += x;
-      }
-      acc += cc;
-      const int64_t i = st + li;
-      if (comp == 0)
-        near[i] = acc;
-      else
-        near[n + 3 * i + comp - 1] = acc;
-    }
-  }
-}
-
-// d/dx_k of sum_i g_i u_i: g_k grad u(x_k) (x_k as a target of the forward
-// pass) + q_k grad v(x_k) (x_k as a source, v = transposed pass with charges
-// g); fields are -grad.
-template <typename T>
-__global__ void k_adjoint_combine(int64_t n, const T* __restrict__ q, const T* __restrict__ g,
-                                  const T* __restrict__ ff, const T* __restrict__ ft,
-                                  T* __restrict__ gx) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= 3 * n) return;
-  const int64_t i = e / 3;
-  gx[e] = -(g[i] * ff[e] + q[i] * ft[e]);
-}
-
 inline unsigned blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
-// The near field (P2P) over the direct lists Ls into near, on stream sp:
-// one launch over the work items, then the partial sums of the leaves whose
-// list was split.
-template <typename T>
-void near_field(fmm_plan* pl, const ListSet& Ls, const Src<T>* src, int64_t n, T* near,
-                bool field, hipStream_t sp, const StageMarks& mk) {
-  mk.begin(kStP2P, sp);
-  const int G = p2p_groups(pl);
-  auto p2p = [&](auto kern) {
-    kern<<<(unsigned)Ls.n_pitems, 64, 0, sp>>>(n, Ls.pitem_leaf, Ls.pitem_kb, Ls.pitem_ke,
-                                               Ls.pitem_out, pl->leaf_start, pl->xs, pl->ys,
-                                               pl->zs, src, Ls.p2p_src, pl->has_dup ? 1 : 0, near,
-                                               (T*)Ls.p2p_part);
-  };
-  if (field) {
-    if (G == 1) p2p(k_p2p<T, true, 1>);
-    else if (G == 2) p2p(k_p2p<T, true, 2>);
-    else p2p(k_p2p<T, true, 4>);
-  } else {
-    if (G == 1) p2p(k_p2p<T, false, 1>);
-    else if (G == 2) p2p(k_p2p<T, false, 2>);
-    else p2p(k_p2p<T, false, 4>);
-  }
-  if (Ls.n_psplit > 0) {
-    auto sum = [&](auto kern) {
-      kern<<<(unsigned)Ls.n_psplit, 64, 0, sp>>>(n, Ls.psplit_leaf, Ls.psplit_first,
-                                                 Ls.psplit_cnt, Ls.pitem_out, pl->leaf_start,
-                                                 (const T*)Ls.p2p_part, near);
-    };
-    if (field) sum(k_p2p_sum<T, true>);
-    else sum(k_p2p_sum<T, false>);
-  }
-  mk.end(kStP2P, sp);
-}
+}  // namespace
 
 // One evaluation: P2P writes the near field in leaf order, L2P adds the far
 // field and writes the outputs.
 template <int P, typename T>
-void run(fmm_plan* pl, const Workspace& ws, int dir, const T* q, T* pot, T* field,
-         hipStream_t st) {
+void run_pass(fmm_plan* pl, const Workspace& ws, int dir, const T* q, T* pot, T* field,
+              hipStream_t st) {
   const int s = pl->s;
   const T* tab = (const T*)pl->tables;
   Src<T>* src = (Src<T>*)ws.src;
@@ -930,7 +685,7 @@ void run(fmm_plan* pl, const Workspace& ws, int dir, const T* q, T* pot, T* fiel
   if (fork) FMM_HIP(hipEventRecord(pl->ev_fork, st));
   auto near_part = [&] {
     if (fork) FMM_HIP(hipStreamWaitEvent(sp, pl->ev_fork, 0));
-    near_field<T>(pl, Ls, src, n, near, field != nullptr, sp, mk);
+    near_field(pl, Ls, src, n, near, field != nullptr, sp, mk);
     if (fork) FMM_HIP(hipEventRecord(pl->ev_join, sp));
   };
   // enqueued after the far-field chain when forked, so that the chain's
@@ -1023,80 +778,9 @@ void run(fmm_plan* pl, const Workspace& ws, int dir, const T* q, T* pot, T* fiel
   FMM_HIP(hipGetLastError());
 }
 
-}  // namespace
-
-bool valid_p2p_groups(const fmm_plan* pl, int g) {
-  return g == 1 || ((g == 2 || g == 4) && pl->max_leaf_count <= 64 / g);
-}
-bool valid_leaves_per_wave(const fmm_plan* pl, int l) {
-  return l == 1 || ((l == 2 || l == 4 || l == 8) && pl->max_leaf_count <= 64 / l);
-}
-int p2p_groups(const fmm_plan* pl) {
-  if (pl->p2p_groups && valid_p2p_groups(pl, pl->p2p_groups)) return pl->p2p_groups;
-  const int m = pl->max_leaf_count;
-  return m > 32 ? 1 : (m > 16 ? 2 : 4);
-}
-int chain_waves(const fmm_plan* pl) {
-  return pl->prm.p < kChainShareMinOrder || pl->chain_waves == 1 ? 1 : kShareWaves;
-}
-int m2l_waves(const fmm_plan* pl) {
-  const int shared = m2l_share_waves(pl->prm.p, pl->prm.precision == FMM_FP64);
-  return pl->m2l_waves == 1 ? 1 : shared;
-}
-int leaves_per_wave(const fmm_plan* pl) {
-  if (pl->leaves_per_wave && valid_leaves_per_wave(pl, pl->leaves_per_wave))
-    return pl->leaves_per_wave;
-  const int m = pl->max_leaf_count;
-  return m > 32 ? 1 : (m > 16 ? 2 : (m > 8 ? 4 : 8));
-}
-
-namespace {
-
-template <typename T>
-void dispatch(int p, fmm_plan* pl, const Workspace& ws, int dir, const T* q, T* pot,
-              T* field, hipStream_t st) {
-  switch (p) {
-#define FMM_CASE(PP) \
-  case PP:           \
-    run<PP, T>(pl, ws, dir, q, pot, field, st); \
-    break;
-    FMM_CASE(1) FMM_CASE(2) FMM_CASE(3) FMM_CASE(4) FMM_CASE(5)
-    FMM_CASE(6) FMM_CASE(7) FMM_CASE(8) FMM_CASE(9) FMM_CASE(10)
-#undef FMM_CASE
-    default:
-      throw Error{FMM_ENOTSUP, "expansion order without compiled kernels"};
-  }
-}
-
-}  // namespace
-
-void evaluate(fmm_plan* pl, const Workspace& ws, int dir, const void* q, int nrhs, void* pot,
-              void* field, hipStream_t st) {
-  // vector r of q has the source side's points, of pot/field the target side's
-  const int64_t nq = src_side(pl, dir).npt, nu = tgt_side(pl, dir).npt;
-  for (int r = 0; r < nrhs; ++r) {
-    if (pl->prm.precision == FMM_FP32) {
-      dispatch<float>(pl->prm.p, pl, ws, dir, (const float*)q + r * nq, (float*)pot + r * nu,
-                      field ? (float*)field + 3 * r * nu : nullptr, st);
-    } else {
-      dispatch<double>(pl->prm.p, pl, ws, dir, (const double*)q + r * nq, (double*)pot + r * nu,
-                       field ? (double*)field + 3 * r * nu : nullptr, st);
-    }
-  }
-}
-
-void adjoint_combine(fmm_plan* pl, const void* q, const void* g, const void* field_fwd,
-                     const void* field_t, void* grad_x, hipStream_t st) {
-  const int64_t n = pl->n;
-  if (pl->prm.precision == FMM_FP32)
-    k_adjoint_combine<float><<<blocks(3 * n, 256), 256, 0, st>>>(
-        n, (const float*)q, (const float*)g, (const float*)field_fwd, (const float*)field_t,
-        (float*)grad_x);
-  else
-    k_adjoint_combine<double><<<blocks(3 * n, 256), 256, 0, st>>>(
-        n, (const double*)q, (const double*)g, (const double*)field_fwd,
-        (const double*)field_t, (double*)grad_x);
-  FMM_HIP(hipGetLastError());
-}
+template void run_pass<FMM_ORDER, double>(fmm_plan*, const Workspace&, int, const double*, double*,
+                                          double*, hipStream_t);
+template void run_pass<FMM_ORDER, float>(fmm_plan*, const Workspace&, int, const float*, float*,
+                                         float*, hipStream_t);
 
 }  // namespace fmm

@@ -58,8 +58,32 @@ struct FinList {
   int64_t n = 0;
 };
 
-// Lanes of one M2L block (one wave).
+// Centre and length scale of a box in one 32-byte record.
+struct alignas(32) BoxGeo {
+  double x, y, z, scale;
+};
+
+// Lanes of one M2L block (one wave), and how many of them hold an item.
 constexpr int kM2LBlock = 64;
+constexpr int m2l_lanes(int, bool) { return kM2LBlock; }
+
+// Near-field work items: item j covers direct pairs [kb[j], ke[j]) of target
+// leaf leaf[j]; every target leaf has at least one.  out[j] < 0: the leaf's
+// only item, written to the near field; otherwise the element offset of the
+// item's partial sums (4 rows of the leaf's point count: potential, field x,
+// y, z) in part.  The split leaves split_leaf[i] add the partials of their
+// split_cnt[i] items from split_first[i] on, in item order.
+struct NearItems {
+  int32_t* leaf = nullptr;
+  int32_t* kb = nullptr;
+  int32_t* ke = nullptr;
+  int64_t* out = nullptr;
+  int32_t* split_leaf = nullptr;
+  int32_t* split_first = nullptr;
+  int32_t* split_cnt = nullptr;
+  void* part = nullptr;
+  int64_t n = 0, n_split = 0;
+};
 
 // Interaction lists of one direction, CSR by target.  M2L work items: lane
 // i covers pairs [item_begin[i], item_end[i]) of target item_tgt[i] (-1 for
@@ -88,28 +112,13 @@ struct ListSet {
   // translation of its parent's final local (when the parent has one).
   FinList fin[2];
   int64_t n_m2l = 0, n_p2p = 0, n_items = 0, n_blocks = 0;
-  // Near-field work items: item j covers direct pairs [pitem_kb[j],
-  // pitem_ke[j]) of target leaf pitem_leaf[j], about kP2PItemWork
-  // interactions or one whole leaf; every target leaf has at least one.
-  // pitem_out[j] < 0: the leaf's only item, written to the near field;
-  // otherwise the element offset of the item's partial sums (4 rows of the
-  // leaf's point count: potential, field x, y, z) in p2p_part.  The split
-  // leaves psplit_leaf[i] add the partials of their psplit_cnt[i] items
-  // from psplit_first[i] on, in item order.
-  int32_t* pitem_leaf = nullptr;
-  int32_t* pitem_kb = nullptr;
-  int32_t* pitem_ke = nullptr;
-  int64_t* pitem_out = nullptr;
-  int32_t* psplit_leaf = nullptr;
-  int32_t* psplit_first = nullptr;
-  int32_t* psplit_cnt = nullptr;
-  void* p2p_part = nullptr;
-  int64_t n_pitems = 0, n_psplit = 0, p2p_part_elems = 0;
+  NearItems near;  // make_p2p_items
 };
 
-// Interactions per near-field work item before a leaf's direct list is
-// split (2^16: the uniform 2^20 cube keeps one item per leaf).
-constexpr int64_t kP2PItemWork = 1 << 16;
+// Near-field work items (make_p2p_items): items wanted, shortest and longest
+// item in interactions, and the number of target leaves that fill the chip.
+constexpr int64_t kP2PItems = 16384, kP2PItemMin = 1 << 12, kP2PItemMax = 1 << 16;
+constexpr int64_t kP2PLeaves = 8192;
 
 // Per-evaluation device buffers (all but the M2L partial rows of the
 // batched form): leaf-ordered source records, expansions, the near field,
@@ -186,6 +195,7 @@ struct fmm_plan {
   double* cz = nullptr;
   double* radius = nullptr;  // [nbox]
   double* scale = nullptr;   // [nbox] length scale of the box's expansions
+  fmm::BoxGeo* geo = nullptr;  // [nbox] cx, cy, cz, scale
   int32_t max_leaf_count = 0;
   bool has_dup = true;  // some two points coincide (set by the tree build)
   // launch tiles (0: the default rule from max_leaf_count; set by
@@ -193,7 +203,7 @@ struct fmm_plan {
   int p2p_groups = 0;
   int leaves_per_wave = 0;
   // 1: one lane per M2L translation; 0: the shared form where it is built
-  // (m2l_share_waves), else one lane
+  // (m2l_shared_built), else one lane
   int m2l_waves = 0;
   // 1: one lane per M2M / L2L translation; 0: shared by four waves from
   // order kChainShareMinOrder on
@@ -316,17 +326,29 @@ void build_tree(fmm_plan* pl, const double* pos, hipStream_t st);
 // between the source tree src and the target tree tgt of the plan (the
 // same tree for a plan over one point set).
 void build_lists(fmm_plan* pl, const TreeDesc& src, const TreeDesc& tgt, hipStream_t st);
-// M2L work items and block segments of one list set from its CSR, and the
-// near-field work items of direction dir (lists.hip).
-void make_items(fmm_plan* pl, ListSet& S, hipStream_t st);
-void make_p2p_items(fmm_plan* pl, int dir, hipStream_t st);
+// Plan with the 32-vector form.
+inline bool batched_plan(const fmm_plan* pl) {
+  return pl->prm.precision == FMM_FP32 && pl->prm.max_rhs > 1 && pl->nsides == 1;
+}
+// Work distribution of direction dir (lists.hip): M2L items, near-field items.
+void make_work(fmm_plan* pl, int dir, hipStream_t st);
 // Operator tables for order p (tables.cpp), cached per process/device.
 const void* get_tables(int p, int precision, int device);
 // Evaluation (eval.hip): dir 0 = G-hat, dir 1 = G-hat^T.
 void evaluate(fmm_plan* pl, const Workspace& ws, int dir, const void* q, int nrhs, void* pot,
               void* field, hipStream_t st);
-// Up to batch_width() FP32 charge vectors in one pass (batch.hip).
+// Up to kBatchWidth FP32 charge vectors in one pass (batch.hip, compiled once
+// per order; batch_near.hip).
+constexpr int kBatchWidth = 32;
 int batch_width();
+void batch_gather(const fmm_plan* pl, const float* q, int R, float* qL, hipStream_t st);
+void batch_near(const fmm_plan* pl, const ListSet& Ls, const float* qL, float* potL, float* fldL,
+                hipStream_t st);
+void batch_scatter(const fmm_plan* pl, int R, const float* potL, const float* fldL, float* pot,
+                   float* field, hipStream_t st);
+template <int P>
+void run_batch(fmm_plan* pl, const ListSet& Ls, const float* q, int R, float* pot, float* field,
+               hipStream_t st);
 // waves per block of the batched near field for this plan
 int batch_p2p_waves(const fmm_plan* pl);
 // iperm of a batched plan from its perm (on st)
@@ -348,6 +370,8 @@ int p2p_groups(const fmm_plan* pl);
 int leaves_per_wave(const fmm_plan* pl);
 int m2l_waves(const fmm_plan* pl);
 int chain_waves(const fmm_plan* pl);
+// waves per translation of the shared forms
+constexpr int kShareWaves = 4;
 // lowest order with the shared M2M / L2L forms
 constexpr int kChainShareMinOrder = 5;
 // Waves per translation of the shared M2L form for order p and precision
@@ -383,6 +407,16 @@ struct StageMarks {
     if (row) FMM_HIP(hipEventRecord((*row)[2 * k + 1], s));
   }
 };
+
+// Near field over the direct lists Ls (near.hip): src holds the leaf-ordered
+// source records of this pass, near receives potential [n] and field [n][3]
+// in leaf order, both of the plan's precision.
+void near_field(fmm_plan* pl, const ListSet& Ls, const void* src, int64_t n, void* near, bool field,
+                hipStream_t sp, const StageMarks& mk);
+// One pass of expansion order P (eval.hip, compiled once per order).
+template <int P, typename T>
+void run_pass(fmm_plan* pl, const Workspace& ws, int dir, const T* q, T* pot, T* field,
+              hipStream_t st);
 
 // Runs f, turning exceptions into a status and the thread's error message
 // (every C entry point).

@@ -23,6 +23,7 @@
 #pragma clang fp contract(off)
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 
 #include "internal.h"
@@ -146,26 +147,41 @@ void keys_to_csr(fmm_plan* pl, Scratch& sc, uint64_t* keys, int64_t nk,
 
 }  // namespace
 
+namespace {
+
+__global__ void k_box_geo(int64_t n, const double* __restrict__ cx, const double* __restrict__ cy,
+                          const double* __restrict__ cz, const double* __restrict__ scale,
+                          BoxGeo* __restrict__ geo) {
+  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (b < n) geo[b] = BoxGeo{cx[b], cy[b], cz[b], scale[b]};
+}
+
 // M2L work items of a list set, packed into blocks of kM2LBlock lanes so
 // that the items of one target always share a block (its partial sums are
 // then added inside the block, in lane order, and written once).  Each
-// target's list is split into ceil(len / kItemPairs) items of equal length
-// (+-1), at most kM2LBlock of them.  Blocks are filled first-fit from a
+// target's list is split into ceil(len / item_pairs) items of equal length
+// (+-1), at most a block of them.  item_pairs is kItemPairs; a FP64 plan of
+// fewer than kItemsFull items of that length (two waves of blocks on every
+// SIMD) takes shorter ones, down to one pair for each wave of a block: an item
+// is a serial chain of translations (about 9 us each at p = 8), and a small
+// plan has idle SIMDs to spread it over (3189 pairs: 108 -> 36 us).  FP32 keeps the length,
+// and with it the order of its sums.  Blocks are filled first-fit from a
 // window of the next kPackWindow targets in box order, which keeps nearby
 // targets (and so their source boxes) in neighbouring blocks while leaving
 // few lanes idle; the lanes a block does not fill get target -1.
-void make_items(fmm_plan* pl, ListSet& S, hipStream_t st) {
-  const int kItemPairs = 12, kPackWindow = 128;
-  std::vector<int32_t> mptr(pl->nbox + 1);
-  FMM_HIP(hipMemcpyAsync(mptr.data(), S.m2l_ptr, sizeof(int32_t) * (pl->nbox + 1),
-                         hipMemcpyDeviceToHost, st));
-  FMM_HIP(hipStreamSynchronize(st));
+void make_items(fmm_plan* pl, ListSet& S, const std::vector<int32_t>& mptr, hipStream_t st) {
+  constexpr int64_t kItemPairs = 12, kItemsFull = 1024 * kM2LBlock;
+  constexpr int kPackWindow = 128;
+  const bool fp64 = pl->prm.precision == FMM_FP64;
+  const int lanes = m2l_lanes(pl->prm.p, fp64);
+  const int item_pairs =
+      (int)(fp64 ? std::min(std::max(S.n_m2l / kItemsFull, (int64_t)2), kItemPairs) : kItemPairs);
   std::vector<int32_t> tg, ni;  // targets with a list, in box order; their item counts
   for (int64_t t = 0; t < pl->nbox; ++t) {
     const int32_t lt = mptr[t + 1] - mptr[t];
     if (lt == 0) continue;
     tg.push_back((int32_t)t);
-    ni.push_back(std::min((lt + kItemPairs - 1) / kItemPairs, kM2LBlock));
+    ni.push_back(std::min((lt + item_pairs - 1) / item_pairs, lanes));
   }
   std::vector<int32_t> it_t, it_b, it_e, first(pl->nbox, 0), cnt(pl->nbox, 0);
   std::vector<int32_t> seg_ptr(1, 0), seg_tgt, seg_lanes;
@@ -173,8 +189,8 @@ void make_items(fmm_plan* pl, ListSet& S, hipStream_t st) {
   size_t j = 0;
   while (j < tg.size()) {
     int used = 0;
-    for (size_t k = j; k < tg.size() && k < j + kPackWindow && used < kM2LBlock; ++k) {
-      if (placed[k] || used + ni[k] > kM2LBlock) continue;
+    for (size_t k = j; k < tg.size() && k < j + kPackWindow && used < lanes; ++k) {
+      if (placed[k] || used + ni[k] > lanes) continue;
       placed[k] = 1;
       const int32_t t = tg[k], lt = mptr[t + 1] - mptr[t];
       first[t] = (int32_t)it_t.size();
@@ -215,23 +231,13 @@ void make_items(fmm_plan* pl, ListSet& S, hipStream_t st) {
   FMM_HIP(hipStreamSynchronize(st));
 }
 
-// Near-field work items of direction dir over the target side's leaves:
-// a leaf's direct list is cut into runs of source leaves of about
-// kP2PItemWork interactions (a run ends before the source leaf that would
-// pass the budget; a run holds at least one leaf), so that leaves with very
-// long lists (clustered points) spread over many blocks.
-void make_p2p_items(fmm_plan* pl, int dir, hipStream_t st) {
-  ListSet& S = pl->lists[dir];
-  const Side& T = tgt_side(pl, dir);
-  std::vector<int32_t> ptr(pl->nleaf + 1), src(std::max<int64_t>(S.n_p2p, 1)), ls(pl->nleaf + 1);
-  FMM_HIP(hipMemcpyAsync(ptr.data(), S.p2p_ptr, sizeof(int32_t) * (pl->nleaf + 1),
-                         hipMemcpyDeviceToHost, st));
-  if (S.n_p2p > 0)
-    FMM_HIP(hipMemcpyAsync(src.data(), S.p2p_src, sizeof(int32_t) * S.n_p2p,
-                           hipMemcpyDeviceToHost, st));
-  FMM_HIP(hipMemcpyAsync(ls.data(), pl->leaf_start, sizeof(int32_t) * (pl->nleaf + 1),
-                         hipMemcpyDeviceToHost, st));
-  FMM_HIP(hipStreamSynchronize(st));
+// Near-field work items over the target side's leaves: a leaf's direct list
+// is cut into runs of source leaves of about `budget` interactions (a run
+// ends before the source leaf that would pass the budget; a run holds at
+// least one leaf).
+NearItems near_items(fmm_plan* pl, const Side& T, const std::vector<int32_t>& ptr,
+                     const std::vector<int32_t>& src, const std::vector<int32_t>& ls,
+                     int64_t budget, hipStream_t st) {
   std::vector<int32_t> il, kb, ke, sl, sf, sc;
   std::vector<int64_t> out;
   int64_t part = 0;
@@ -242,7 +248,7 @@ void make_p2p_items(fmm_plan* pl, int dir, hipStream_t st) {
     int64_t acc = 0;
     for (int32_t k = ptr[t]; k < ptr[t + 1]; ++k) {
       const int64_t w = nt * (int64_t)(ls[src[k] + 1] - ls[src[k]]);
-      if (k > b && acc + w > kP2PItemWork) {
+      if (k > b && acc + w > budget) {
         il.push_back((int32_t)t);
         kb.push_back(b);
         ke.push_back(k);
@@ -273,22 +279,74 @@ void make_p2p_items(fmm_plan* pl, int dir, hipStream_t st) {
       FMM_HIP(hipMemcpyAsync(d, v.data(), sizeof(int32_t) * v.size(), hipMemcpyHostToDevice, st));
     return d;
   };
-  S.n_pitems = (int64_t)il.size();
-  S.n_psplit = (int64_t)sl.size();
-  S.pitem_leaf = up32(il);
-  S.pitem_kb = up32(kb);
-  S.pitem_ke = up32(ke);
-  S.psplit_leaf = up32(sl);
-  S.psplit_first = up32(sf);
-  S.psplit_cnt = up32(sc);
-  S.pitem_out = (int64_t*)plan_alloc(pl, sizeof(int64_t) * std::max<size_t>(out.size(), 1));
+  NearItems N;
+  N.n = (int64_t)il.size();
+  N.n_split = (int64_t)sl.size();
+  N.leaf = up32(il);
+  N.kb = up32(kb);
+  N.ke = up32(ke);
+  N.split_leaf = up32(sl);
+  N.split_first = up32(sf);
+  N.split_cnt = up32(sc);
+  N.out = (int64_t*)plan_alloc(pl, sizeof(int64_t) * std::max<size_t>(out.size(), 1));
   if (!out.empty())
-    FMM_HIP(hipMemcpyAsync(S.pitem_out, out.data(), sizeof(int64_t) * out.size(),
-                           hipMemcpyHostToDevice, st));
-  S.p2p_part_elems = part;
+    FMM_HIP(hipMemcpyAsync(N.out, out.data(), sizeof(int64_t) * out.size(), hipMemcpyHostToDevice,
+                           st));
   const size_t es = pl->prm.precision == FMM_FP32 ? sizeof(float) : sizeof(double);
-  S.p2p_part = part > 0 ? plan_alloc(pl, es * (size_t)part) : nullptr;
+  N.part = part > 0 ? plan_alloc(pl, es * (size_t)part) : nullptr;
   FMM_HIP(hipStreamSynchronize(st));
+  return N;
+}
+
+// The near-field items of one direction.  Budget: kP2PItemMax (long lists of
+// clustered points spread over many blocks; 2^16 interactions take about
+// 30 us on a SIMD of their own, and the uniform 2^20 cube keeps one item
+// per leaf).  A plan of few interactions takes a kP2PItems-th of them, at
+// least kP2PItemMin (a run about as long as its set-up), so that it fills
+// the chip; with kP2PLeaves leaves or more whole lists do (every
+// part of a split list writes and re-reads a partial row).  FP32 keeps the
+// long runs: the rounding of its compensated sums, and with it the energy
+// gradients handed out in FP64, then do not depend on this choice.
+void make_p2p_items(fmm_plan* pl, ListSet& S, const Side& T, const std::vector<int32_t>& ls,
+                    hipStream_t st) {
+  std::vector<int32_t> ptr(pl->nleaf + 1), src(std::max<int64_t>(S.n_p2p, 1));
+  FMM_HIP(hipMemcpyAsync(ptr.data(), S.p2p_ptr, sizeof(int32_t) * (pl->nleaf + 1),
+                         hipMemcpyDeviceToHost, st));
+  if (S.n_p2p > 0)
+    FMM_HIP(hipMemcpyAsync(src.data(), S.p2p_src, sizeof(int32_t) * S.n_p2p,
+                           hipMemcpyDeviceToHost, st));
+  FMM_HIP(hipStreamSynchronize(st));
+  int64_t total = 0;
+  for (int64_t t = T.leaf0; t < T.leaf0 + T.nleaf; ++t) {
+    int64_t len = 0;
+    for (int32_t k = ptr[t]; k < ptr[t + 1]; ++k) len += ls[src[k] + 1] - ls[src[k]];
+    total += len * (ls[t + 1] - ls[t]);
+  }
+  pl->p2p_inter = total;  // the same in both directions
+  int64_t budget = kP2PItemMax;
+  if (pl->prm.precision == FMM_FP64 && T.nleaf < kP2PLeaves)
+    budget = std::min(std::max(total / kP2PItems, kP2PItemMin), kP2PItemMax);
+  S.near = near_items(pl, T, ptr, src, ls, budget, st);
+}
+
+}  // namespace
+
+void make_work(fmm_plan* pl, int dir, hipStream_t st) {
+  ListSet& S = pl->lists[dir];
+  std::vector<int32_t> mptr(pl->nbox + 1), ls(pl->nleaf + 1);
+  FMM_HIP(hipMemcpyAsync(mptr.data(), S.m2l_ptr, sizeof(int32_t) * (pl->nbox + 1),
+                         hipMemcpyDeviceToHost, st));
+  FMM_HIP(hipMemcpyAsync(ls.data(), pl->leaf_start, sizeof(int32_t) * (pl->nleaf + 1),
+                         hipMemcpyDeviceToHost, st));
+  if (!pl->geo) {
+    pl->geo = (BoxGeo*)plan_alloc(pl, sizeof(BoxGeo) * pl->nbox);
+    k_box_geo<<<blocks(pl->nbox, 256), 256, 0, st>>>(pl->nbox, pl->cx, pl->cy, pl->cz, pl->scale,
+                                                     pl->geo);
+    FMM_HIP(hipGetLastError());
+  }
+  FMM_HIP(hipStreamSynchronize(st));
+  make_items(pl, S, mptr, st);
+  make_p2p_items(pl, S, tgt_side(pl, dir), ls, st);
 }
 
 void build_lists(fmm_plan* pl, const TreeDesc& ts, const TreeDesc& tt, hipStream_t st) {
@@ -449,26 +507,6 @@ void build_lists(fmm_plan* pl, const TreeDesc& ts, const TreeDesc& tt, hipStream
   k_transposed_keys<<<blocks(pl->nleaf, T), T, 0, st>>>(pl->nleaf, F.p2p_ptr, F.p2p_src, tk);
   keys_to_csr(pl, sc, tk, np, pl->nleaf, &A.p2p_src, &A.p2p_ptr, st);
   FMM_HIP(hipGetLastError());
-
-  // P2P interaction count (same in both directions)
-  std::vector<int32_t> pptr(pl->nleaf + 1), psrc(std::max<int64_t>(np, 1)),
-      lstart(pl->nleaf + 1);
-  FMM_HIP(hipMemcpyAsync(pptr.data(), F.p2p_ptr, sizeof(int32_t) * (pl->nleaf + 1),
-                         hipMemcpyDeviceToHost, st));
-  FMM_HIP(hipMemcpyAsync(psrc.data(), F.p2p_src, sizeof(int32_t) * psrc.size(),
-                         hipMemcpyDeviceToHost, st));
-  FMM_HIP(hipMemcpyAsync(lstart.data(), pl->leaf_start, sizeof(int32_t) * (pl->nleaf + 1),
-                         hipMemcpyDeviceToHost, st));
-  FMM_HIP(hipStreamSynchronize(st));
-  int64_t inter = 0;
-  for (int64_t t = 0; t < pl->nleaf; ++t)
-    for (int32_t k = pptr[t]; k < pptr[t + 1]; ++k)
-      inter += (int64_t)(lstart[t + 1] - lstart[t]) * (lstart[psrc[k] + 1] - lstart[psrc[k]]);
-  pl->p2p_inter = inter;
-  make_items(pl, F, st);
-  make_items(pl, A, st);
-  make_p2p_items(pl, 0, st);
-  make_p2p_items(pl, 1, st);
 }
 
 }  // namespace fmm

@@ -4,8 +4,8 @@
 // plan).  The union concatenates every per-point, per-box and per-leaf array
 // in problem order and shifts the indices stored in them (point, box, leaf
 // and list-pair ids) by the running totals, so that every evaluation stage
-// runs as one launch over the work of all problems; the M2L work items are
-// then packed over the union's lists.
+// runs as one launch over the work of all problems; the M2L and near-field
+// work is then distributed over the union's lists.
 #include <algorithm>
 
 #include "internal.h"
@@ -47,7 +47,6 @@ void build_union(fmm_plan* U, const std::vector<const fmm_plan*>& subs, hipStrea
   U->nbox = 0;
   U->nleaf = 0;
   U->L = 0;
-  U->p2p_inter = 0;
   U->max_leaf_count = 0;
   U->has_dup = false;
   int64_t n_m2l[2] = {0, 0}, n_p2p[2] = {0, 0};
@@ -56,7 +55,6 @@ void build_union(fmm_plan* U, const std::vector<const fmm_plan*>& subs, hipStrea
     U->nbox += p->nbox;
     U->nleaf += p->nleaf;
     U->L = std::max(U->L, p->L);
-    U->p2p_inter += p->p2p_inter;
     U->max_leaf_count = std::max(U->max_leaf_count, p->max_leaf_count);
     U->has_dup = U->has_dup || p->has_dup;
     for (int d = 0; d < 2; ++d) {
@@ -126,10 +124,7 @@ void build_union(fmm_plan* U, const std::vector<const fmm_plan*>& subs, hipStrea
   // mix targets of different problems
   U->side[0].npt = U->n;
   U->side[0].nleaf = U->nleaf;
-  make_items(U, U->lists[0], st);
-  make_items(U, U->lists[1], st);
-  make_p2p_items(U, 0, st);
-  make_p2p_items(U, 1, st);
+  for (int d = 0; d < 2; ++d) make_work(U, d, st);
 }
 
 }  // namespace fmm

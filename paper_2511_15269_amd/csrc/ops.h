@@ -609,34 +609,6 @@ __device__ __forceinline__ double inv_sqrt(double r2) {
 }
 __device__ __forceinline__ float inv_sqrt(float r2) { return __builtin_amdgcn_rsqf(r2); }
 
-// ------------------------------------------------------ M2L partial sums
-// D[t][0..W) = sum over the M2L work items of box t (in item order) of
-// their partial rows, for every box t in boxes[0..nb): one block per box,
-// threads over the row.  The far-field local of every box starts here; the
-// level-by-level L2L kernels then add the translated parent local.
-template <typename T>
-__global__ void k_psum(int64_t nb, const int32_t* __restrict__ boxes,
-                       const int32_t* __restrict__ item_first, const int32_t* __restrict__ item_cnt,
-                       const T* __restrict__ partial, int W, T* __restrict__ D) {
-  const int64_t t = boxes[blockIdx.x];
-  const int b = item_first[t], e = b + item_cnt[t];
-  for (int k = threadIdx.x; k < W; k += blockDim.x) {
-    T acc = T(0);
-    int it = b;
-    // four rows' loads in flight at a time; the sum keeps item order
-    for (; it + 4 <= e; it += 4) {
-      const T r0 = partial[(int64_t)it * W + k], r1 = partial[(int64_t)(it + 1) * W + k];
-      const T r2 = partial[(int64_t)(it + 2) * W + k], r3 = partial[(int64_t)(it + 3) * W + k];
-      acc += r0;
-      acc += r1;
-      acc += r2;
-      acc += r3;
-    }
-    for (; it < e; ++it) acc += partial[(int64_t)it * W + k];
-    D[t * W + k] = acc;
-  }
-}
-
 // ------------------------------------------------------ block placement
 // Workgroups are handed to the 8 XCDs round robin (block b to XCD b % 8),
 // each XCD with its own L2.  This maps block b to a logical index so that

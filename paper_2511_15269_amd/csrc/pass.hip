@@ -1,0 +1,97 @@
+// One evaluation pass of a plan: the launch tiles in effect, the choice of
+// the order's kernels (eval.hip) and the adjoint's combine step.
+#include "internal.h"
+
+namespace fmm {
+
+bool valid_p2p_groups(const fmm_plan* pl, int g) {
+  return g == 1 || ((g == 2 || g == 4) && pl->max_leaf_count <= 64 / g);
+}
+bool valid_leaves_per_wave(const fmm_plan* pl, int l) {
+  return l == 1 || ((l == 2 || l == 4 || l == 8) && pl->max_leaf_count <= 64 / l);
+}
+int p2p_groups(const fmm_plan* pl) {
+  if (pl->p2p_groups && valid_p2p_groups(pl, pl->p2p_groups)) return pl->p2p_groups;
+  const int m = pl->max_leaf_count;
+  return m > 32 ? 1 : (m > 16 ? 2 : 4);
+}
+int chain_waves(const fmm_plan* pl) {
+  return pl->prm.p < kChainShareMinOrder || pl->chain_waves == 1 ? 1 : kShareWaves;
+}
+int m2l_waves(const fmm_plan* pl) {
+  const int shared = m2l_share_waves(pl->prm.p, pl->prm.precision == FMM_FP64);
+  return pl->m2l_waves == 1 ? 1 : shared;
+}
+int leaves_per_wave(const fmm_plan* pl) {
+  if (pl->leaves_per_wave && valid_leaves_per_wave(pl, pl->leaves_per_wave))
+    return pl->leaves_per_wave;
+  const int m = pl->max_leaf_count;
+  return m > 32 ? 1 : (m > 16 ? 2 : (m > 8 ? 4 : 8));
+}
+
+namespace {
+
+// d/dx_k of sum_i g_i u_i: g_k grad u(x_k) (x_k as a target of the forward
+// pass) + q_k grad v(x_k) (x_k as a source, v = transposed pass with charges
+// g); fields are -grad.
+template <typename T>
+__global__ void k_adjoint_combine(int64_t n, const T* __restrict__ q, const T* __restrict__ g,
+                                  const T* __restrict__ ff, const T* __restrict__ ft,
+                                  T* __restrict__ gx) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= 3 * n) return;
+  const int64_t i = e / 3;
+  gx[e] = -(g[i] * ff[e] + q[i] * ft[e]);
+}
+
+
+inline unsigned blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
+
+template <typename T>
+void dispatch(int p, fmm_plan* pl, const Workspace& ws, int dir, const T* q, T* pot,
+              T* field, hipStream_t st) {
+  switch (p) {
+#define FMM_CASE(PP) \
+  case PP:           \
+    run_pass<PP, T>(pl, ws, dir, q, pot, field, st); \
+    break;
+    FMM_CASE(1) FMM_CASE(2) FMM_CASE(3) FMM_CASE(4) FMM_CASE(5)
+    FMM_CASE(6) FMM_CASE(7) FMM_CASE(8) FMM_CASE(9) FMM_CASE(10)
+#undef FMM_CASE
+    default:
+      throw Error{FMM_ENOTSUP, "expansion order without compiled kernels"};
+  }
+}
+
+}  // namespace
+
+void evaluate(fmm_plan* pl, const Workspace& ws, int dir, const void* q, int nrhs, void* pot,
+              void* field, hipStream_t st) {
+  // vector r of q has the source side's points, of pot/field the target side's
+  const int64_t nq = src_side(pl, dir).npt, nu = tgt_side(pl, dir).npt;
+  for (int r = 0; r < nrhs; ++r) {
+    if (pl->prm.precision == FMM_FP32) {
+      dispatch<float>(pl->prm.p, pl, ws, dir, (const float*)q + r * nq, (float*)pot + r * nu,
+                      field ? (float*)field + 3 * r * nu : nullptr, st);
+    } else {
+      dispatch<double>(pl->prm.p, pl, ws, dir, (const double*)q + r * nq, (double*)pot + r * nu,
+                       field ? (double*)field + 3 * r * nu : nullptr, st);
+    }
+  }
+}
+
+void adjoint_combine(fmm_plan* pl, const void* q, const void* g, const void* field_fwd,
+                     const void* field_t, void* grad_x, hipStream_t st) {
+  const int64_t n = pl->n;
+  if (pl->prm.precision == FMM_FP32)
+    k_adjoint_combine<float><<<blocks(3 * n, 256), 256, 0, st>>>(
+        n, (const float*)q, (const float*)g, (const float*)field_fwd, (const float*)field_t,
+        (float*)grad_x);
+  else
+    k_adjoint_combine<double><<<blocks(3 * n, 256), 256, 0, st>>>(
+        n, (const double*)q, (const double*)g, (const double*)field_fwd,
+        (const double*)field_t, (double*)grad_x);
+  FMM_HIP(hipGetLastError());
+}
+
+}  // namespace fmm
