@@ -376,9 +376,11 @@ fmm_status fmm_plan_autotune(fmm_plan* plan, const void* q, void* stream, int* p
  *   leaves_per_wave  leaves per wave of P2M and L2P: 1, 2, 4 or 8 (at most
  *                    64 / value points per leaf)
  *   m2l_waves        waves sharing each M2L translation (Sec. II.D): 1 (one
- *                    lane per translation) or 4, the shared form, which
- *                    exists for FP64 at p = 6, 7 and FP32 at p = 9, 10 and
- *                    is their default.  Both forms give identical results.
+ *                    lane per translation) or 4, which is accepted for FP64
+ *                    at p = 6, 7 and FP32 at p = 9, 10 and is their default.
+ *                    The shared form is built where it is faster (FP32,
+ *                    p = 10); elsewhere both values run the one-lane form.
+ *                    Identical results.
  *   chain_waves      waves sharing each M2M and L2L translation: 1 (one
  *                    lane per translation) or 4 (the shared form, built and
  *                    the default for p >= 5).  Identical results.

@@ -312,105 +312,108 @@ __global__ __launch_bounds__(64 * kShareWaves) void k_m2m_shared(
 }
 
 // ---------------------------------------------------------------- M2L
-// Lane-private LDS rows as in P2M (row r of lane l at r * kRow + l): the
-// segment sums below read different rows of the same lane without bank
-// conflicts, while a wave's access to one row stays contiguous.
-
 // For every target segment of this block (seg_tgt[g], lanes
-// [seg_lanes[g] & 255, seg_lanes[g] >> 8), g in [sb, se)), adds rows
-// [0, NR) of buf over the segment's lanes in lane order and stores the sums
-// as coefficients k0 .. k0 + NR - 1 of the target's local.
-template <int NR, typename T>
-__device__ __forceinline__ void segment_sums(const T* buf, int k0, int K, int sb, int se,
+// [seg_lanes[g] & 255, seg_lanes[g] >> 8), g in [sb, se)), adds the K rows
+// (coefficients; row r of lane l at r * STRIDE + l, an odd stride, so that
+// reads of different rows of one lane hit different banks) over the
+// segment's lanes in lane order and stores the sums as the target's local.
+template <int K, int STRIDE, typename T>
+__device__ __forceinline__ void segment_sums(const T* buf, int sb, int se,
                                              const int32_t* __restrict__ seg_tgt,
                                              const int32_t* __restrict__ seg_lanes, T* D) {
-  const int n = (se - sb) * NR;
+  const int n = (se - sb) * K;
   for (int idx = threadIdx.x; idx < n; idx += blockDim.x) {
-    const int g = sb + idx / NR, r = idx % NR;
+    const int g = sb + idx / K, r = idx % K;
     const int info = seg_lanes[g];
     T acc = T(0);
-    for (int l = info & 255; l < (info >> 8); ++l) acc += buf[r * kRow + l];
-    D[(int64_t)seg_tgt[g] * K + k0 + r] = acc;
+    for (int l = info & 255; l < (info >> 8); ++l) acc += buf[r * STRIDE + l];
+    D[(int64_t)seg_tgt[g] * K + r] = acc;
   }
 }
 
-// One block = kM2LBlock lanes; lane = one work item (a run of at most a
-// dozen source boxes of one target).  Every lane translates its sources and
-// sums them; the items of one target share the block and their sums are
+// Waves of a block of the one-lane form: they share the block's accumulators.
+constexpr int m2l_block_waves(bool fp64) { return fp64 ? 2 : 4; }
+// Waves per SIMD it is held to: the most that the registers of a translation
+// (one expansion, the products' partial results, the geometry) allow without
+// spilling.
+constexpr int m2l_waves_per_simd(int p, bool fp64) {
+  return fp64 ? (p <= 5 ? 4 : p == 6 ? 3 : p <= 8 ? 2 : 1)
+              : (p <= 5 ? 6 : p == 6 ? 5 : p <= 8 ? 4 : p == 9 ? 3 : 2);
+}
+
+// Lane l of the W waves of a block = work item l (a run of at most a dozen
+// source boxes of one target); wave w translates the item's pairs w, w + W,
+// w + 2 W, ... and adds them to the item's row of accumulators in LDS, the
+// waves one after another (barriers), so that an item's pairs are added in
+// list order.  The items of one target share the block and their sums are
 // added in lane order into the target's local, D_t = sum of its M2L
 // translations, written once (no partial rows in memory).
-template <int P, typename T>
-__global__ __launch_bounds__(kM2LBlock) void k_m2l(
-    int64_t nblocks, const int32_t* __restrict__ item_tgt,
-    const int32_t* __restrict__ item_begin, const int32_t* __restrict__ item_end,
-    const int32_t* __restrict__ seg_ptr, const int32_t* __restrict__ seg_tgt,
-    const int32_t* __restrict__ seg_lanes, const int32_t* __restrict__ src,
-    const double* __restrict__ cx, const double* __restrict__ cy,
-    const double* __restrict__ cz, const double* __restrict__ scale,
-    const T* __restrict__ C, const T* __restrict__ tab, T* __restrict__ D) {
+// Bound by the latencies of one wave: the operator tables come through the
+// scalar unit about every 16 (FP64) multiply-adds, and a lane's expansion
+// fills the registers, so what counts is the number of waves on a SIMD.
+// Accumulators shared by W waves and registers held to one expansion (pins
+// in the translation steps) give two waves in FP64 at p = 8 (81 x 63
+// accumulators of 8 bytes, 40 KB for two waves) and four in FP32, where one
+// wave per accumulator set gave one and two.  Measured (uniform cube 2^20,
+// 3.4 M pairs, p = 8): FP64 0.55 -> 0.45 ms, FP32 0.36 (one wave per
+// accumulator set, otherwise alike) -> 0.28 ms; W = 1 in FP64 0.53 ms.
+template <int P, typename T, int W>
+__global__ __launch_bounds__(kM2LBlock* W)
+    __attribute__((amdgpu_waves_per_eu(m2l_waves_per_simd(P, sizeof(T) == 8)))) void k_m2l(
+        const int32_t* __restrict__ item_tgt, const int32_t* __restrict__ item_begin,
+        const int32_t* __restrict__ item_end, const int32_t* __restrict__ seg_ptr,
+        const int32_t* __restrict__ seg_tgt, const int32_t* __restrict__ seg_lanes,
+        const int32_t* __restrict__ src, const BoxGeo* __restrict__ geo,
+        const T* __restrict__ C, const T* __restrict__ tab, T* __restrict__ D) {
   constexpr int K = K_<P>::value;
+  constexpr int S = m2l_lanes(P, sizeof(T) == 8) | 1;  // row stride (odd)
+  __shared__ T acc[(K - 1) * S + m2l_lanes(P, sizeof(T) == 8)];
   const int64_t b = xcd_block(blockIdx.x, gridDim.x);
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x % kM2LBlock;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kM2LBlock);
+  for (int e = threadIdx.x; e < (int)(sizeof(acc) / sizeof(T)); e += kM2LBlock * W) acc[e] = T(0);
   const int64_t i = b * kM2LBlock + lane;
-  const int t = item_tgt[i];
-  const int jb = item_begin[i], je = item_end[i];  // empty for idle lanes
-  const int tt = t < 0 ? 0 : t;
-  const double tx = cx[tt], ty = cy[tt], tz = cz[tt], rt = scale[tt];
-  // Accumulators: in FP64 with (p+1)^2 > KL the first KL coefficients live
-  // in lane-private LDS rows (78 rows of 65 doubles fit 40 KiB, so four
-  // 64-lane blocks fill a CU's 160 KiB, the occupancy the registers allow
-  // anyway) and are updated with LDS atomic adds that need no registers; the
-  // rest stay in registers.  The rows are then reused to add the items of
-  // each target.
-  constexpr int KL = (sizeof(T) == 8 && K > 78) ? 78 : 0;
-  constexpr int KR = K - KL;                      // accumulators in registers
-  constexpr int CH = KL > 0 ? (KR < KL ? KR : KL) : (KR < 16 ? KR : 16);  // rows per pass
-  constexpr int NROW = KL > 0 ? KL : CH;
-  __shared__ T accl[(NROW - 1) * kRow + kM2LBlock];
-  T acc[KR];
+  const int tgt = max(item_tgt[i], 0);
+  const int jb = item_begin[i], len = item_end[i] - jb;  // len 0 for idle lanes
+  // pairs of the longest item of the block (the same in every wave)
+  int longest = len;
 #pragma unroll
-  for (int k = 0; k < KL; ++k) accl[k * kRow + lane] = T(0);
-#pragma unroll
-  for (int k = 0; k < KR; ++k) acc[k] = T(0);
-  for (int j = jb; j < je; ++j) {
-    const int sidx = src[j];
+  for (int off = 1; off < kM2LBlock; off <<= 1) longest = max(longest, __shfl_xor(longest, off, 64));
+  longest = __builtin_amdgcn_readfirstlane(longest);
+  for (int j = w; j - w < longest; j += W) {
+    // lanes past their item's end translate its last pair (or the list's
+    // first) once more and add nothing: no divergence around the translation
+    const int sb = src[jb + max(min(j, len - 1), 0)];
+    int tb = tgt;
+    pin(tb);  // read again every round: no registers for it in between
+    const BoxGeo gs = geo[sb], gt = geo[tb];
     T v[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = C[(int64_t)sidx * K + k];
-    rotate_shift<P, kM2L, T>(v, cx[sidx] - tx, cy[sidx] - ty, cz[sidx] - tz, scale[sidx], rt,
-                             tab);
+    for (int k = 0; k < K; ++k) v[k] = C[(int64_t)sb * K + k];
+    rotate_shift<P, kM2L, T>(v, gs.x - gt.x, gs.y - gt.y, gs.z - gt.z, gs.scale, gt.scale, tab);
+    // finished here, not moved behind the barriers
 #pragma unroll
-    for (int k = 0; k < KL; ++k)
-      __hip_atomic_fetch_add(&accl[k * kRow + lane], v[k], __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_WORKGROUP);
-    {
-      // a plain add: whether the compiler would fuse it with the last
-      // product of the translation depends on the surrounding code
-#pragma clang fp contract(off)
+    for (int k = 0; k < K; ++k) pin(v[k]);
+    __syncthreads();
 #pragma unroll
-      for (int k = KL; k < K; ++k) acc[k - KL] += v[k];
+    for (int u = 0; u < W; ++u) {
+      if (w == u && j < len) {
+        int at = lane;
+        pin(at);  // no addresses held over the translation
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          if (sizeof(T) == 8)  // an LDS add needs no register
+            __hip_atomic_fetch_add(&acc[k * S + at], v[k], __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+          else  // (in FP32 it would be a compare-and-swap loop)
+            acc[k * S + at] += v[k];
+        }
+      }
+      if (u + 1 < W) __syncthreads();
     }
   }
-  const int sb = seg_ptr[b], se = seg_ptr[b + 1];
   __syncthreads();
-  if (KL > 0) {
-    segment_sums<(KL > 0 ? KL : 1), T>(accl, 0, K, sb, se, seg_tgt, seg_lanes, D);
-    __syncthreads();
-  }
-  // register accumulators, CH rows at a time
-#pragma unroll
-  for (int c0 = 0; c0 < KR; c0 += CH) {
-#pragma unroll
-    for (int r = 0; r < CH; ++r)
-      if (c0 + r < KR) accl[r * kRow + lane] = acc[c0 + r];
-    __syncthreads();
-    if (c0 + CH <= KR)
-      segment_sums<CH, T>(accl, KL + c0, K, sb, se, seg_tgt, seg_lanes, D);
-    else
-      segment_sums<(KR % CH > 0 ? KR % CH : 1), T>(accl, KL + c0, K, sb, se, seg_tgt,
-                                                   seg_lanes, D);
-    __syncthreads();
-  }
+  segment_sums<K, S, T>(acc, seg_ptr[b], seg_ptr[b + 1], seg_tgt, seg_lanes, D);
 }
 
 template <int P, typename T, int NW, int W>
@@ -446,10 +449,13 @@ __device__ __forceinline__ void m2l_share(int lane, int jb, int je, int iters, d
 
 // The same M2L items with the translation of each item shared by the NW
 // waves of a block (turn_shared): lane l of every wave works on item l.
-// Gives the same results as k_m2l.
+// Gives the same results as k_m2l.  Built where the one-lane form is left
+// with two waves per SIMD in FP32 (p = 10: 0.64 against 0.72 ms for 4.2 M
+// pairs; at p = 9 it is the slower one, 0.57 against 0.49, as in FP64 at
+// p = 6 and 7, 0.43 against 0.29 and 0.68 against 0.45).
 template <int P, typename T, int NW>
 __global__ __launch_bounds__(kM2LBlock * NW) void k_m2l_shared(
-    int64_t nblocks, const int32_t* __restrict__ item_tgt,
+    const int32_t* __restrict__ item_tgt,
     const int32_t* __restrict__ item_begin, const int32_t* __restrict__ item_end,
     const int32_t* __restrict__ seg_ptr, const int32_t* __restrict__ seg_tgt,
     const int32_t* __restrict__ seg_lanes, const int32_t* __restrict__ src,
@@ -487,7 +493,7 @@ __global__ __launch_bounds__(kM2LBlock * NW) void k_m2l_shared(
   }
 #undef FMM_M2L_WAVE
   __syncthreads();
-  segment_sums<K, T>(X, 0, K, seg_ptr[b], seg_ptr[b + 1], seg_tgt, seg_lanes, D);
+  segment_sums<K, kRow, T>(X, seg_ptr[b], seg_ptr[b + 1], seg_tgt, seg_lanes, D);
 }
 
 // ---------------------------------------------------------------- L2L
@@ -708,19 +714,25 @@ void run_pass(fmm_plan* pl, const Workspace& ws, int dir, const T* q, T* pot, T*
   mk.end(kStM2M, st);
   mk.begin(kStM2L, st);
   if (Ls.n_blocks > 0) {
-    auto m2l = [&](auto kern, int nw) {
+    [[maybe_unused]] auto shared_form = [&](auto kern, int nw) {
       kern<<<(unsigned)Ls.n_blocks, kM2LBlock * nw, 0, st>>>(
-          Ls.n_blocks, Ls.item_tgt, Ls.item_begin, Ls.item_end, Ls.seg_ptr, Ls.seg_tgt,
-          Ls.seg_lanes, Ls.m2l_src, pl->cx, pl->cy, pl->cz, pl->scale, C, tab, D);
+          Ls.item_tgt, Ls.item_begin, Ls.item_end, Ls.seg_ptr, Ls.seg_tgt, Ls.seg_lanes,
+          Ls.m2l_src, pl->cx, pl->cy, pl->cz, pl->scale, C, tab, D);
     };
-    constexpr int NW = m2l_share_waves(P, sizeof(T) == 8);
-    if constexpr (NW > 1) {
+    auto one_lane = [&] {
+      constexpr int W = m2l_block_waves(sizeof(T) == 8);
+      k_m2l<P, T, W><<<(unsigned)Ls.n_blocks, kM2LBlock * W, 0, st>>>(
+          Ls.item_tgt, Ls.item_begin, Ls.item_end, Ls.seg_ptr, Ls.seg_tgt, Ls.seg_lanes,
+          Ls.m2l_src, pl->geo, C, tab, D);
+    };
+    if constexpr (m2l_shared_built(P, sizeof(T) == 8)) {
+      constexpr int NW = m2l_share_waves(P, sizeof(T) == 8);
       if (m2l_waves(pl) > 1)
-        m2l(k_m2l_shared<P, T, NW>, NW);
+        shared_form(k_m2l_shared<P, T, NW>, NW);
       else
-        m2l(k_m2l<P, T>, 1);
+        one_lane();
     } else {
-      m2l(k_m2l<P, T>, 1);
+      one_lane();
     }
   }
   mk.end(kStM2L, st);

@@ -63,9 +63,11 @@ struct alignas(32) BoxGeo {
   double x, y, z, scale;
 };
 
-// Lanes of one M2L block (one wave), and how many of them hold an item.
+// Lanes of one M2L block (every wave of it), and how many of them hold an
+// item: all, except in FP64 at p = 8, where 63 rows of 81 accumulators let
+// four blocks of two waves share a CU's LDS (160 KB).
 constexpr int kM2LBlock = 64;
-constexpr int m2l_lanes(int, bool) { return kM2LBlock; }
+constexpr int m2l_lanes(int p, bool fp64) { return fp64 && p == 8 ? 63 : kM2LBlock; }
 
 // Near-field work items: item j covers direct pairs [kb[j], ke[j]) of target
 // leaf leaf[j]; every target leaf has at least one.  out[j] < 0: the leaf's
@@ -374,15 +376,14 @@ int chain_waves(const fmm_plan* pl);
 constexpr int kShareWaves = 4;
 // lowest order with the shared M2M / L2L forms
 constexpr int kChainShareMinOrder = 5;
-// Waves per translation of the shared M2L form for order p and precision
-// (1: no shared form).  It is built where it was measured faster than one
-// lane per translation: FP64 at p = 6, 7 (above, its LDS tile caps the
-// occupancy; below, one lane per translation keeps two waves per SIMD
-// anyway) and FP32 at p = 9, 10 (where the one-lane form runs out of
-// registers).
+// Values of the m2l_waves tile besides 1 for order p and precision (1: none).
+// 4 asks for the form whose translations are shared by four waves; it is
+// built (m2l_shared_built) where it is the faster one, and both values run
+// the one-lane form elsewhere.
 constexpr int m2l_share_waves(int p, bool fp64) {
   return fp64 ? ((p == 6 || p == 7) ? 4 : 1) : (p >= 9 ? 4 : 1);
 }
+constexpr bool m2l_shared_built(int p, bool fp64) { return !fp64 && p == 10; }
 bool valid_p2p_groups(const fmm_plan* pl, int g);
 bool valid_leaves_per_wave(const fmm_plan* pl, int l);
 

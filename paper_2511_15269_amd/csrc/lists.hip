@@ -164,7 +164,7 @@ __global__ void k_box_geo(int64_t n, const double* __restrict__ cx, const double
 // fewer than kItemsFull items of that length (two waves of blocks on every
 // SIMD) takes shorter ones, down to one pair for each wave of a block: an item
 // is a serial chain of translations (about 9 us each at p = 8), and a small
-// plan has idle SIMDs to spread it over (3189 pairs: 108 -> 36 us).  FP32 keeps the length,
+// plan has idle SIMDs to spread it over (3189 pairs: 108 -> 19 us).  FP32 keeps the length,
 // and with it the order of its sums.  Blocks are filled first-fit from a
 // window of the next kPackWindow targets in box order, which keeps nearby
 // targets (and so their source boxes) in neighbouring blocks while leaving

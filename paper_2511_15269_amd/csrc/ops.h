@@ -65,6 +65,14 @@ struct TabReader {
   }
 };
 
+// Ends the computation of x here: code that follows in the source is not
+// moved in front of it.  Without it the compiler spreads a translation's
+// independent steps over each other and holds the values of several at once.
+template <typename T>
+__device__ __forceinline__ void pin(T& x) {
+  asm volatile("" : "+v"(x));
+}
+
 // The translation steps below (azimuth, apply_y, zshift, Turn) do not let
 // the compiler fuse a product with an addition on its own: every fused
 // multiply-add is written out, so the rounding of each coefficient is fixed
@@ -88,14 +96,23 @@ struct All_ {
 template <int P, typename T, int SGN, int Q, unsigned DM = All_<P>::value>
 __device__ __forceinline__ void azimuth(T* v, T c1, T s1) {
 #pragma clang fp contract(off)
+  // formed anew at every call: kept from one call to the next they would
+  // hold 4 P registers over the whole translation
+  pin(c1);
+  pin(s1);
   T cm = T(1), sm = T(0);
 #pragma unroll
   for (int m = 1; m <= P; ++m) {
     if ((DM >> m) == 0) break;  // no degree >= m in the mask
-    const T cn = fma(cm, c1, -(sm * s1));
-    const T sn = fma(sm, c1, cm * s1);
-    cm = cn;
-    sm = sn;
+    if (m == 1) {
+      cm = c1;
+      sm = s1;
+    } else {
+      const T cn = fma(cm, c1, -(sm * s1));
+      const T sn = fma(sm, c1, cm * s1);
+      cm = cn;
+      sm = sn;
+    }
     T c, s;
     if (Q == 0) {
       c = cm;
@@ -157,7 +174,10 @@ __device__ __forceinline__ void apply_y(T* v, const T* __restrict__ tab) {
       }
     }
 #pragma unroll
-    for (int a = -n; a <= n; ++a) v[cidx(n, a)] = u[a + n];
+    for (int a = -n; a <= n; ++a) {
+      pin(u[a + n]);
+      v[cidx(n, a)] = u[a + n];
+    }
   }
 }
 
@@ -171,19 +191,17 @@ enum { kM2M = 0, kM2L = 1, kL2L = 2 };
 template <int P, int KIND, typename T, unsigned OM = All_<P>::value>
 __device__ __forceinline__ void zshift(T* v, T a, T b, const T* __restrict__ tab) {
 #pragma clang fp contract(off)
-  T pa[2 * P + 2], pb[P + 2];
-  pa[0] = T(1);
-  pb[0] = T(1);
-#pragma unroll
-  for (int j = 1; j <= P; ++j) pa[j] = pa[j - 1] * a;
-#pragma unroll
-  for (int j = 1; j <= P + 1; ++j) pb[j] = pb[j - 1] * b;
   if (KIND == kM2L) {
+    // the powers of a and b are formed as they are used (no arrays of them
+    // held over the products)
+    T pw = T(1);
 #pragma unroll
-    for (int n = 0; n <= P; ++n)
+    for (int n = 1; n <= P; ++n) {
+      pw *= a;
 #pragma unroll
       for (int m = -n; m <= n; ++m)
-        if ((OM >> (m < 0 ? -m : m)) & 1u) v[cidx(n, m)] *= pa[n];
+        if ((OM >> (m < 0 ? -m : m)) & 1u) v[cidx(n, m)] *= pw;
+    }
     // table column by column (k outer): independent accumulators; the
     // blocks of -m and +m are the same, read twice in a row
 #pragma unroll
@@ -204,9 +222,27 @@ __device__ __forceinline__ void zshift(T* v, T a, T b, const T* __restrict__ tab
         }
       }
 #pragma unroll
-      for (int n = am; n <= P; ++n) v[cidx(n, m)] = m < 0 ? -(o[n] * pb[n + 1]) : o[n] * pb[n + 1];
+      for (int n = am; n <= P; ++n) {
+        pin(o[n]);
+        v[cidx(n, m)] = m < 0 ? -o[n] : o[n];
+      }
+    }
+    pw = T(1);
+#pragma unroll
+    for (int n = 0; n <= P; ++n) {
+      pw *= b;
+#pragma unroll
+      for (int m = -n; m <= n; ++m)
+        if ((OM >> (m < 0 ? -m : m)) & 1u) v[cidx(n, m)] *= pw;
     }
   } else {
+    T pa[P + 1], pb[P + 2];
+    pa[0] = T(1);
+    pb[0] = T(1);
+#pragma unroll
+    for (int j = 1; j <= P; ++j) pa[j] = pa[j - 1] * a;
+#pragma unroll
+    for (int j = 1; j <= P + 1; ++j) pb[j] = pb[j - 1] * b;
     if (KIND == kM2M) {
 #pragma unroll
       for (int n = 0; n <= P; ++n)
