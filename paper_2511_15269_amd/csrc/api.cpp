@@ -2,7 +2,9 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <map>
 #include <memory>
+#include <mutex>
 #include <new>
 
 #include "internal.h"
@@ -49,12 +51,41 @@ void dev_free(fmm_plan* pl, void* p) {
 }
 
 void* plan_alloc(fmm_plan* pl, size_t bytes) {
-  void* p = dev_alloc(pl, bytes);
   bytes = bytes ? bytes : 16;
-  pl->bufs.push_back(DevBuf{p, bytes});
-  pl->device_bytes += bytes;
-  return p;
+  if (!pl->allocator.alloc)
+    if (void* p = pl->arena.take(bytes)) return p;
+  // block shared by small arrays: 1 MB, then 4 MB each
+  const size_t shared = (size_t)(pl->bufs.empty() ? 1 : 4) << 20;
+  const bool own = pl->allocator.alloc != nullptr || bytes > shared / 2;
+  const size_t block = own ? bytes : shared;
+  void* p = dev_alloc(pl, block);
+  pl->bufs.push_back(DevBuf{p, block});
+  pl->device_bytes += block;
+  if (own) return p;
+  pl->arena = Arena{(char*)p, block};
+  return pl->arena.take(bytes);
 }
+
+namespace {
+
+// Second stream of an evaluation with its fork / join events.  Making and
+// destroying a stream takes about 0.6 ms each, so a destroyed plan's are kept
+// for the next one on the device, kForkPool of them at most.
+struct Fork {
+  hipStream_t stream;
+  hipEvent_t fork, join;
+};
+constexpr size_t kForkPool = 8;
+std::mutex g_fork_mu;
+std::map<int, std::vector<Fork>> g_forks;  // device -> idle forks
+
+void destroy_fork(const Fork& f) {
+  if (f.fork) (void)hipEventDestroy(f.fork);
+  if (f.join) (void)hipEventDestroy(f.join);
+  if (f.stream) (void)hipStreamDestroy(f.stream);
+}
+
+}  // namespace
 
 WorkspaceLayout workspace_layout(int64_t n, int64_t nbox, const fmm_params& prm, bool batched) {
   const size_t es = prm.precision == FMM_FP32 ? sizeof(float) : sizeof(double);
@@ -108,17 +139,42 @@ void release_profile(fmm_plan* pl) {
 void plan_free_all(fmm_plan* pl) {
   for (auto& b : pl->bufs) dev_free(pl, b.ptr);
   pl->bufs.clear();
+  pl->arena = Arena{};
   pl->device_bytes = 0;
-  if (pl->ev_fork) (void)hipEventDestroy(pl->ev_fork);
-  if (pl->ev_join) (void)hipEventDestroy(pl->ev_join);
-  if (pl->side_stream) (void)hipStreamDestroy(pl->side_stream);
+  const Fork f{pl->side_stream, pl->ev_fork, pl->ev_join};
   pl->ev_fork = pl->ev_join = nullptr;
   pl->side_stream = nullptr;
+  // kept only whole, idle and outside any capture (an abandoned capture
+  // would otherwise reach the next plan)
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  bool keep = f.stream && f.fork && f.join &&
+              hipStreamIsCapturing(f.stream, &cap) == hipSuccess &&
+              cap == hipStreamCaptureStatusNone && hipStreamQuery(f.stream) == hipSuccess;
+  if (!keep) (void)hipGetLastError();
+  if (keep) {
+    std::lock_guard<std::mutex> lk(g_fork_mu);
+    std::vector<Fork>& idle = g_forks[pl->device];
+    keep = idle.size() < kForkPool;
+    if (keep) idle.push_back(f);
+  }
+  if (!keep) destroy_fork(f);
 }
 
 // The evaluation's second stream and its fork / join events (on the
 // plan's device, which is current during creation).
 void make_fork(fmm_plan* pl) {
+  {
+    std::lock_guard<std::mutex> lk(g_fork_mu);
+    std::vector<Fork>& idle = g_forks[pl->device];
+    if (!idle.empty()) {
+      const Fork f = idle.back();
+      idle.pop_back();
+      pl->side_stream = f.stream;
+      pl->ev_fork = f.fork;
+      pl->ev_join = f.join;
+      return;
+    }
+  }
   FMM_HIP(hipStreamCreateWithFlags(&pl->side_stream, hipStreamNonBlocking));
   FMM_HIP(hipEventCreateWithFlags(&pl->ev_fork, hipEventDisableTiming));
   FMM_HIP(hipEventCreateWithFlags(&pl->ev_join, hipEventDisableTiming));
@@ -127,38 +183,31 @@ void make_fork(fmm_plan* pl) {
 void make_steps(fmm_plan* pl, const std::vector<std::vector<TreeDesc>>& groups,
                 hipStream_t st) {
   const int s = pl->s;
-  auto upload = [&](const std::vector<int32_t>& v) {
-    int32_t* d = (int32_t*)plan_alloc(pl, sizeof(int32_t) * v.size());
-    if (!v.empty())
-      FMM_HIP(hipMemcpyAsync(d, v.data(), sizeof(int32_t) * v.size(), hipMemcpyHostToDevice, st));
-    FMM_HIP(hipStreamSynchronize(st));
-    return d;
-  };
+  Upload up;
   std::vector<int32_t> lb;
   for (const auto& trees : groups)
     for (const TreeDesc& t : trees) {
       const int64_t nl = t.level_off[t.L + 1] - t.level_off[t.L];
       for (int64_t i = 0; i < nl; ++i) lb.push_back((int32_t)(t.box_base + t.level_off[t.L] + i));
     }
-  pl->leaf_box = upload(lb);
+  up.add(lb, &pl->leaf_box);
   // Boxes whose expansions matter: those in an M2L pair (either role, so
   // both the forward and the transposed pass are covered) and all their
   // descendants.  Multipoles of other boxes are never read; locals of other
   // non-leaf boxes are zero and are not formed (children skip the
   // translation from them).
   std::vector<char> active(pl->nbox, 0);
+  std::vector<int32_t> mptr[2];  // M2L list offsets of the two directions
   {
-    const ListSet& F = pl->lists[0];
-    std::vector<int32_t> ptr(pl->nbox + 1), src(std::max<int64_t>(F.n_m2l, 1));
-    FMM_HIP(hipMemcpyAsync(ptr.data(), F.m2l_ptr, sizeof(int32_t) * (pl->nbox + 1),
-                           hipMemcpyDeviceToHost, st));
-    if (F.n_m2l > 0)
-      FMM_HIP(hipMemcpyAsync(src.data(), F.m2l_src, sizeof(int32_t) * F.n_m2l,
-                             hipMemcpyDeviceToHost, st));
+    // targets of the transposed lists: the boxes that are sources
+    for (int d = 0; d < 2; ++d) {
+      mptr[d].resize(pl->nbox + 1);
+      FMM_HIP(hipMemcpyAsync(mptr[d].data(), pl->lists[d].m2l_ptr,
+                             sizeof(int32_t) * (pl->nbox + 1), hipMemcpyDeviceToHost, st));
+    }
     FMM_HIP(hipStreamSynchronize(st));
     for (int64_t b = 0; b < pl->nbox; ++b)
-      if (ptr[b + 1] > ptr[b]) active[b] = 1;
-    for (int64_t k = 0; k < F.n_m2l; ++k) active[src[k]] = 1;
+      if (mptr[0][b + 1] > mptr[0][b] || mptr[1][b + 1] > mptr[1][b]) active[b] = 1;
     for (const auto& trees : groups)
       for (const TreeDesc& t : trees)
         for (int l = 1; l <= t.L; ++l)
@@ -168,6 +217,12 @@ void make_steps(fmm_plan* pl, const std::vector<std::vector<TreeDesc>>& groups,
           }
   }
   std::vector<std::vector<int32_t>> all_of(groups.size());
+  struct LevelStep {
+    std::vector<Step>* of;
+    size_t i;
+    std::vector<int32_t> a, b;
+  };
+  std::vector<LevelStep> steps;
   for (size_t g = 0; g < groups.size(); ++g) {
     const std::vector<TreeDesc>& trees = groups[g];
     Side& S = pl->side[g];
@@ -190,18 +245,17 @@ void make_steps(fmm_plan* pl, const std::vector<std::vector<TreeDesc>>& groups,
         }
       }
       if (a.empty()) continue;
-      Step St;
-      St.n = (int64_t)a.size();
-      St.a = upload(a);
-      St.b = upload(b);
-      S.m2m_steps.push_back(St);
+      S.m2m_steps.emplace_back();
+      S.m2m_steps.back().n = (int64_t)a.size();
+      steps.push_back({&S.m2m_steps, S.m2m_steps.size() - 1, std::move(a), std::move(b)});
     }
     // Downward: every box whose local is formed starts from the sum of its
     // M2L translations (written by the M2L kernel, or zero); step l then
     // adds the translated parent local to the boxes of level l of every tree
     // that deep whose parent has one.
+    // (only the 32-vector form walks these levels)
     std::vector<int32_t>& all = all_of[g];
-    for (int l = 0; l <= Lmax; ++l) {
+    for (int l = 0; l <= Lmax && batched_plan(pl); ++l) {
       std::vector<int32_t> a, b;
       for (const TreeDesc& t : trees) {
         if (l > t.L) continue;
@@ -217,15 +271,17 @@ void make_steps(fmm_plan* pl, const std::vector<std::vector<TreeDesc>>& groups,
         }
       }
       if (a.empty()) continue;
-      Step St;
-      St.n = (int64_t)a.size();
-      St.a = upload(a);
-      St.b = upload(b);
-      S.l2l_steps.push_back(St);
+      S.l2l_steps.emplace_back();
+      S.l2l_steps.back().n = (int64_t)a.size();
+      steps.push_back({&S.l2l_steps, S.l2l_steps.size() - 1, std::move(a), std::move(b)});
     }
     S.l2l_sum.n = (int64_t)all.size();
-    S.l2l_sum.a = upload(all);
+    up.add(all, &S.l2l_sum.a);
     S.l2l_sum.b = nullptr;
+  }
+  for (const LevelStep& e : steps) {  // the vectors of steps have their final size
+    up.add(e.a, &(*e.of)[e.i].a);
+    up.add(e.b, &(*e.of)[e.i].b);
   }
   // Final locals of each direction's target side.  Re-centring a truncated
   // local expansion is exact, so a box's final local is its own M2L sum plus
@@ -235,10 +291,7 @@ void make_steps(fmm_plan* pl, const std::vector<std::vector<TreeDesc>>& groups,
   for (int d = 0; d < 2; ++d) {
     ListSet& L = pl->lists[d];
     const std::vector<TreeDesc>& trees = groups[pl->nsides == 1 ? 0 : 1 - d];
-    std::vector<int32_t> ptr(pl->nbox + 1);
-    FMM_HIP(hipMemcpyAsync(ptr.data(), L.m2l_ptr, sizeof(int32_t) * (pl->nbox + 1),
-                           hipMemcpyDeviceToHost, st));
-    FMM_HIP(hipStreamSynchronize(st));
+    const std::vector<int32_t>& ptr = mptr[d];
     auto has = [&](int64_t b) { return ptr[b + 1] > ptr[b]; };
     std::vector<int32_t> box[2], own[2];
     std::vector<std::vector<int32_t>> src[2];
@@ -284,11 +337,12 @@ void make_steps(fmm_plan* pl, const std::vector<std::vector<TreeDesc>>& groups,
       FinList& F = L.fin[k];
       F.gs = gs;
       F.n = (int64_t)box[k].size();
-      F.box = upload(box[k]);
-      F.own = upload(own[k]);
-      F.anc = upload(flat);
+      up.add(box[k], &F.box);
+      up.add(own[k], &F.own);
+      up.add(flat, &F.anc);
     }
   }
+  up.flush(pl, st);
 }
 
 namespace {

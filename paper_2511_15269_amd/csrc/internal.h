@@ -7,6 +7,7 @@
 #include <exception>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/fmm.h"
@@ -35,6 +36,23 @@ void clear_error();
 struct DevBuf {
   void* ptr = nullptr;
   size_t bytes = 0;
+};
+
+// Part of a device block that is handed out in 256-byte aligned pieces: a
+// plan is some dozens of small arrays, and each hipMalloc and hipFree takes
+// about 10 us.
+struct Arena {
+  char* at = nullptr;
+  size_t left = 0;
+  // the next piece, or NULL when the block has no room for it
+  void* take(size_t bytes) {
+    bytes = (bytes + 255) / 256 * 256;
+    if (bytes > left) return nullptr;
+    char* p = at;
+    at += bytes;
+    left -= bytes;
+    return p;
+  }
 };
 
 // Constant operator tables of one expansion order (values in double; the
@@ -240,6 +258,7 @@ struct fmm_plan {
   const void* tables = nullptr;  // device operator tables for (p, precision)
 
   std::vector<fmm::DevBuf> bufs;
+  fmm::Arena arena;  // small arrays (plans with a caller's allocator: none)
   size_t device_bytes = 0;
   // device memory source of the plan (fmm_plan_create_ex), also used for
   // temporaries during the build; stream passed to the callbacks
@@ -274,12 +293,25 @@ void plan_free_all(fmm_plan* pl);
 // Temporary device memory during the build, through the plan's allocator.
 void* dev_alloc(fmm_plan* pl, size_t bytes);
 void dev_free(fmm_plan* pl, void* p);
-// Temporaries of one build step, released when it goes out of scope.
+// Temporaries of one build step, released when it goes out of scope.  Taken
+// in blocks of growing size (one by one from a caller's allocator).
 struct Scratch {
   fmm_plan* pl;
   std::vector<void*> ptrs;
-  explicit Scratch(fmm_plan* p) : pl(p) {}
+  Arena arena;
+  size_t block;  // size of the next block
+  explicit Scratch(fmm_plan* p, size_t expect = 0) : pl(p), block(((size_t)4 << 20) + expect) {}
   void* get(size_t bytes) {
+    bytes = bytes ? bytes : 16;
+    if (!pl->allocator.alloc) {
+      if (void* p = arena.take(bytes)) return p;
+      if (bytes <= block) {
+        arena = Arena{(char*)dev_alloc(pl, block), block};
+        ptrs.push_back(arena.at);
+        block *= 2;
+        return arena.take(bytes);
+      }
+    }
     void* p = dev_alloc(pl, bytes);
     ptrs.push_back(p);
     return p;
@@ -288,6 +320,30 @@ struct Scratch {
     // the build's kernels may still read them: wait for the stream first
     if (!ptrs.empty()) (void)hipStreamSynchronize(pl->alloc_stream);
     for (void* p : ptrs) dev_free(pl, p);
+  }
+};
+
+// Index arrays of a plan gathered on the host and sent in one copy: add()
+// names the pointer to set, flush() allocates, copies (the host buffer is
+// free again when it returns) and sets them.
+struct Upload {
+  std::vector<int32_t> host;
+  std::vector<std::pair<int32_t**, size_t>> dst;
+  void add(const std::vector<int32_t>& v, int32_t** p) {
+    dst.emplace_back(p, host.size());
+    host.insert(host.end(), v.begin(), v.end());
+    host.resize((host.size() + 63) / 64 * 64);  // 256-byte aligned pieces
+  }
+  void flush(fmm_plan* pl, hipStream_t st) {
+    int32_t* d = (int32_t*)plan_alloc(pl, sizeof(int32_t) * host.size());
+    if (!host.empty()) {
+      FMM_HIP(hipMemcpyAsync(d, host.data(), sizeof(int32_t) * host.size(), hipMemcpyHostToDevice,
+                             st));
+      FMM_HIP(hipStreamSynchronize(st));
+    }
+    for (auto& e : dst) *e.first = d + e.second;
+    host.clear();
+    dst.clear();
   }
 };
 

@@ -64,6 +64,7 @@ __global__ void k_expand_test(int64_t np, int nch, int refine_src, int test,
   double lhs = big + theta * small;
   double rhs = theta * d;
   adm[e] = (test && lhs <= rhs && d > 0.0) ? 1 : 0;
+  if (e == 0) adm[np * nch] = 0;  // its scan is the count of all verdicts
 }
 
 __global__ void k_compact(int64_t ne, const int32_t* __restrict__ cs,
@@ -113,14 +114,23 @@ __global__ void k_csr(int64_t nk, const uint64_t* __restrict__ keys,
 inline unsigned blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 
-// (source << 32 | target) keys of a CSR list: the reversed pairs.
-__global__ void k_transposed_keys(int64_t ntgt, const int32_t* __restrict__ ptr,
+// (source << 32 | target) keys of a CSR list: the reversed pairs.  Thread =
+// pair; its target by bisection (one thread per target took 0.1 ms on lists
+// of a few hundred sources).
+__global__ void k_transposed_keys(int64_t nk, int64_t ntgt, const int32_t* __restrict__ ptr,
                                   const int32_t* __restrict__ src,
                                   uint64_t* __restrict__ keys) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= ntgt) return;
-  for (int32_t k = ptr[t]; k < ptr[t + 1]; ++k)
-    keys[k] = ((uint64_t)src[k] << 32) | (uint64_t)t;
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= nk) return;
+  int64_t lo = 0, hi = ntgt;  // last target with ptr <= k
+  while (hi - lo > 1) {
+    const int64_t mid = (lo + hi) / 2;
+    if (ptr[mid] <= k)
+      lo = mid;
+    else
+      hi = mid;
+  }
+  keys[k] = ((uint64_t)src[k] << 32) | (uint64_t)lo;
 }
 
 int bits_for(int64_t v) {
@@ -214,21 +224,16 @@ void make_items(fmm_plan* pl, ListSet& S, const std::vector<int32_t>& mptr, hipS
   }
   S.n_items = (int64_t)it_t.size();
   S.n_blocks = S.n_items / kM2LBlock;
-  auto up = [&](const std::vector<int32_t>& v) {
-    int32_t* d = (int32_t*)plan_alloc(pl, sizeof(int32_t) * std::max<size_t>(v.size(), 1));
-    if (!v.empty())
-      FMM_HIP(hipMemcpyAsync(d, v.data(), sizeof(int32_t) * v.size(), hipMemcpyHostToDevice, st));
-    return d;
-  };
-  S.item_tgt = up(it_t);
-  S.item_begin = up(it_b);
-  S.item_end = up(it_e);
-  S.item_first = up(first);
-  S.item_cnt = up(cnt);
-  S.seg_ptr = up(seg_ptr);
-  S.seg_tgt = up(seg_tgt);
-  S.seg_lanes = up(seg_lanes);
-  FMM_HIP(hipStreamSynchronize(st));
+  Upload up;
+  up.add(it_t, &S.item_tgt);
+  up.add(it_b, &S.item_begin);
+  up.add(it_e, &S.item_end);
+  up.add(first, &S.item_first);
+  up.add(cnt, &S.item_cnt);
+  up.add(seg_ptr, &S.seg_ptr);
+  up.add(seg_tgt, &S.seg_tgt);
+  up.add(seg_lanes, &S.seg_lanes);
+  up.flush(pl, st);
 }
 
 // Near-field work items over the target side's leaves: a leaf's direct list
@@ -273,21 +278,17 @@ NearItems near_items(fmm_plan* pl, const Side& T, const std::vector<int32_t>& pt
     sf.push_back((int32_t)first);
     sc.push_back((int32_t)cnt);
   }
-  auto up32 = [&](const std::vector<int32_t>& v) {
-    int32_t* d = (int32_t*)plan_alloc(pl, sizeof(int32_t) * std::max<size_t>(v.size(), 1));
-    if (!v.empty())
-      FMM_HIP(hipMemcpyAsync(d, v.data(), sizeof(int32_t) * v.size(), hipMemcpyHostToDevice, st));
-    return d;
-  };
   NearItems N;
   N.n = (int64_t)il.size();
   N.n_split = (int64_t)sl.size();
-  N.leaf = up32(il);
-  N.kb = up32(kb);
-  N.ke = up32(ke);
-  N.split_leaf = up32(sl);
-  N.split_first = up32(sf);
-  N.split_cnt = up32(sc);
+  Upload up;
+  up.add(il, &N.leaf);
+  up.add(kb, &N.kb);
+  up.add(ke, &N.ke);
+  up.add(sl, &N.split_leaf);
+  up.add(sf, &N.split_first);
+  up.add(sc, &N.split_cnt);
+  up.flush(pl, st);
   N.out = (int64_t*)plan_alloc(pl, sizeof(int64_t) * std::max<size_t>(out.size(), 1));
   if (!out.empty())
     FMM_HIP(hipMemcpyAsync(N.out, out.data(), sizeof(int64_t) * out.size(), hipMemcpyHostToDevice,
@@ -352,7 +353,7 @@ void make_work(fmm_plan* pl, int dir, hipStream_t st) {
 void build_lists(fmm_plan* pl, const TreeDesc& ts, const TreeDesc& tt, hipStream_t st) {
   const int Ls = ts.L, Lt = tt.L, nch = pl->nch;
   const int T = 256;
-  Scratch sc(pl);
+  Scratch sc(pl, 100 * (size_t)pl->n);
   // level-mean radii, summed in box order on the host
   std::vector<double> rad(pl->nbox);
   FMM_HIP(hipMemcpyAsync(rad.data(), pl->radius, sizeof(double) * pl->nbox,
@@ -431,21 +432,20 @@ void build_lists(fmm_plan* pl, const TreeDesc& ts, const TreeDesc& tt, hipStream
     const int64_t ne = np * nch;
     int32_t* cs = (int32_t*)sc.get(sizeof(int32_t) * ne);
     int32_t* ct = (int32_t*)sc.get(sizeof(int32_t) * ne);
-    int32_t* adm = (int32_t*)sc.get(sizeof(int32_t) * ne);
-    int32_t* excl = (int32_t*)sc.get(sizeof(int32_t) * ne);
+    int32_t* adm = (int32_t*)sc.get(sizeof(int32_t) * (ne + 1));
+    int32_t* excl = (int32_t*)sc.get(sizeof(int32_t) * (ne + 1));
     const int64_t off_s = ts.box_base + ts.level_off[ls], off_t = tt.box_base + tt.level_off[lt];
     k_expand_test<<<blocks(ne, T), T, 0, st>>>(
         np, nch, src_side ? 1 : 0, test ? 1 : 0, ps, pt, off_s, off_t,
         pl->cx, pl->cy, pl->cz, pl->radius, pl->prm.theta, cs, ct, adm);
     FMM_HIP(hipGetLastError());
-    size_t tb = scan_i32_temp(ne);
+    size_t tb = scan_i32_temp(ne + 1);
     void* tmp = sc.get(tb);
-    exclusive_scan_i32(tmp, tb, adm, excl, ne, st);
-    int32_t last_excl = 0, last_adm = 0;
-    FMM_HIP(hipMemcpyAsync(&last_excl, excl + ne - 1, sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    FMM_HIP(hipMemcpyAsync(&last_adm, adm + ne - 1, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    exclusive_scan_i32(tmp, tb, adm, excl, ne + 1, st);
+    int32_t count = 0;
+    FMM_HIP(hipMemcpyAsync(&count, excl + ne, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     FMM_HIP(hipStreamSynchronize(st));
-    const int64_t nadm = (int64_t)last_excl + last_adm;
+    const int64_t nadm = count;
     uint64_t* keys = (uint64_t*)sc.get(sizeof(uint64_t) * std::max<int64_t>(nadm, 1));
     int32_t* ns = (int32_t*)sc.get(sizeof(int32_t) * std::max<int64_t>(ne - nadm, 1));
     int32_t* nt = (int32_t*)sc.get(sizeof(int32_t) * std::max<int64_t>(ne - nadm, 1));
@@ -502,9 +502,11 @@ void build_lists(fmm_plan* pl, const TreeDesc& ts, const TreeDesc& tt, hipStream
   F.n_p2p = A.n_p2p = np;
   // transposed lists: every (source, target) pair reversed
   uint64_t* tk = (uint64_t*)sc.get(sizeof(uint64_t) * std::max<int64_t>(std::max(n_m2l, np), 1));
-  k_transposed_keys<<<blocks(pl->nbox, T), T, 0, st>>>(pl->nbox, F.m2l_ptr, F.m2l_src, tk);
+  if (n_m2l > 0)
+    k_transposed_keys<<<blocks(n_m2l, T), T, 0, st>>>(n_m2l, pl->nbox, F.m2l_ptr, F.m2l_src, tk);
   keys_to_csr(pl, sc, tk, n_m2l, pl->nbox, &A.m2l_src, &A.m2l_ptr, st);
-  k_transposed_keys<<<blocks(pl->nleaf, T), T, 0, st>>>(pl->nleaf, F.p2p_ptr, F.p2p_src, tk);
+  if (np > 0)
+    k_transposed_keys<<<blocks(np, T), T, 0, st>>>(np, pl->nleaf, F.p2p_ptr, F.p2p_src, tk);
   keys_to_csr(pl, sc, tk, np, pl->nleaf, &A.p2p_src, &A.p2p_ptr, st);
   FMM_HIP(hipGetLastError());
 }

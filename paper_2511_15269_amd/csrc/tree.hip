@@ -101,6 +101,8 @@ __global__ void k_split_prep(int nseg, const int32_t* __restrict__ seg_start,
   pivot[b] = half < cnt ? rank[(int64_t)a * n + la[st + half]] : INT_MAX;
 }
 
+// blockIdx.y: one of the lists that a launch covers, each of n entries, one
+// after another in list, flag, excl and out.
 __global__ void k_flags(int n, const int32_t* __restrict__ list,
                         const int32_t* __restrict__ seg_of,
                         const int32_t* __restrict__ axis,
@@ -109,8 +111,9 @@ __global__ void k_flags(int n, const int32_t* __restrict__ list,
                         int32_t* __restrict__ flag) {
   int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n) return;
+  const int64_t o = (int64_t)blockIdx.y * n;
   int s = seg_of[j];
-  flag[j] = rank[(int64_t)axis[s] * n + list[j]] < pivot[s] ? 1 : 0;
+  flag[o + j] = rank[(int64_t)axis[s] * n + list[o + j]] < pivot[s] ? 1 : 0;
 }
 
 __global__ void k_scatter(int n, const int32_t* __restrict__ list,
@@ -121,11 +124,12 @@ __global__ void k_scatter(int n, const int32_t* __restrict__ list,
                           int32_t* __restrict__ out) {
   int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n) return;
+  const int64_t o = (int64_t)blockIdx.y * n;
   int s = seg_of[j];
   int st = seg_start[s], cnt = seg_start[s + 1] - st, half = (cnt + 1) / 2;
-  int lower_before = excl[j] - excl[st];
-  int dst = flag[j] ? st + lower_before : st + half + (j - st - lower_before);
-  out[dst] = list[j];
+  int lower_before = excl[o + j] - excl[o + st];
+  int dst = flag[o + j] ? st + lower_before : st + half + (j - st - lower_before);
+  out[o + dst] = list[o + j];
 }
 
 __global__ void k_seg_update(int n, const int32_t* __restrict__ seg_start,
@@ -189,18 +193,19 @@ void build_tree(fmm_plan* pl, const double* pos, hipStream_t st) {
   const int n = (int)pl->n;
   const int L = pl->L, s = pl->s;
   const int T = 256;
-  Scratch sc(pl);
+  Scratch sc(pl, 160 * (size_t)n);
   double* X = (double*)sc.get(sizeof(double) * 3 * (size_t)n);
   uint64_t* keys = (uint64_t*)sc.get(sizeof(uint64_t) * 3 * (size_t)n);
   uint64_t* keys_out = (uint64_t*)sc.get(sizeof(uint64_t) * (size_t)n);
   int32_t* iota = (int32_t*)sc.get(sizeof(int32_t) * (size_t)n);
   int32_t* rank = (int32_t*)sc.get(sizeof(int32_t) * 3 * (size_t)n);
-  int32_t* lists[4];
-  int32_t* lists2[4];
-  for (int a = 0; a < 4; ++a) {
-    lists[a] = (int32_t*)sc.get(sizeof(int32_t) * (size_t)n);
-    lists2[a] = (int32_t*)sc.get(sizeof(int32_t) * (size_t)n);
-  }
+  // the four lists one after another, and a second set to partition into; a
+  // launch of a split covers all four while their 4 n entries can be counted
+  // in 32 bits with room to spare
+  const int per = n < (1 << 28) ? 4 : 1;
+  int32_t* base = (int32_t*)sc.get(sizeof(int32_t) * 4 * (size_t)n);
+  int32_t* base2 = (int32_t*)sc.get(sizeof(int32_t) * 4 * (size_t)n);
+  auto list = [&](int a) { return base + (size_t)a * n; };
   int* bad = (int*)sc.get(sizeof(int));
   FMM_HIP(hipMemsetAsync(bad, 0, sizeof(int), st));
 
@@ -215,73 +220,77 @@ void build_tree(fmm_plan* pl, const double* pos, hipStream_t st) {
   void* temp = sc.get(tb);
   for (int a = 0; a < 3; ++a) {
     sort_pairs_u64_i32(temp, tb, keys + (size_t)a * n, keys_out, iota,
-                       lists[a], n, st);
-    k_ranks<<<blocks(n, T), T, 0, st>>>(lists[a], n, rank + (size_t)a * n);
+                       list(a), n, st);
+    k_ranks<<<blocks(n, T), T, 0, st>>>(list(a), n, rank + (size_t)a * n);
   }
-  FMM_HIP(hipMemcpyAsync(lists[3], iota, sizeof(int32_t) * n,
+  FMM_HIP(hipMemcpyAsync(list(3), iota, sizeof(int32_t) * n,
                          hipMemcpyDeviceToDevice, st));
 
   const int64_t maxseg = (int64_t)1 << (L * s);
-  int32_t* seg_start_d = (int32_t*)sc.get(sizeof(int32_t) * (maxseg + 1));
   int32_t* seg_of = (int32_t*)sc.get(sizeof(int32_t) * (size_t)n);
   int32_t* axis = (int32_t*)sc.get(sizeof(int32_t) * maxseg);
   int32_t* pivot = (int32_t*)sc.get(sizeof(int32_t) * maxseg);
-  int32_t* flag = (int32_t*)sc.get(sizeof(int32_t) * (size_t)n);
-  int32_t* excl = (int32_t*)sc.get(sizeof(int32_t) * (size_t)n);
-  size_t sb = scan_i32_temp(n);
+  int32_t* flag = (int32_t*)sc.get(sizeof(int32_t) * per * (size_t)n);
+  int32_t* excl = (int32_t*)sc.get(sizeof(int32_t) * per * (size_t)n);
+  size_t sb = scan_i32_temp((int64_t)per * n);
   void* stemp = sc.get(sb);
   FMM_HIP(hipMemsetAsync(seg_of, 0, sizeof(int32_t) * n, st));
 
-  std::vector<int32_t> seg = {0, n};
-  auto upload_segs = [&]() {
-    FMM_HIP(hipMemcpyAsync(seg_start_d, seg.data(), sizeof(int32_t) * seg.size(),
-                           hipMemcpyHostToDevice, st));
-    // seg is rewritten on the host before the next upload
-    FMM_HIP(hipStreamSynchronize(st));
-  };
-  upload_segs();
-  for (int d = 0; d < L * s; ++d) {
+  // segment starts of every split depth (they follow from n alone), depth d
+  // at segs[d]; sent once
+  std::vector<int32_t> seg = {0, n}, all_segs;
+  std::vector<size_t> segs;
+  for (int d = 0; d <= L * s; ++d) {
+    segs.push_back(all_segs.size());
+    all_segs.insert(all_segs.end(), seg.begin(), seg.end());
+    if (d == L * s) break;
     const int nseg = (int)seg.size() - 1;
-    if (d % s == 0) {
-      int l = d / s;
-      k_geometry<<<blocks(nseg, T), T, 0, st>>>(
-          nseg, seg_start_d, lists[0], lists[1], lists[2], X, n,
-          pl->level_off[l], pl->cx, pl->cy, pl->cz, pl->radius);
-    }
-    k_split_prep<<<blocks(nseg, T), T, 0, st>>>(nseg, seg_start_d, lists[0],
-                                                lists[1], lists[2], X, n, rank,
-                                                axis, pivot);
-    for (int a = 0; a < 4; ++a) {
-      k_flags<<<blocks(n, T), T, 0, st>>>(n, lists[a], seg_of, axis, pivot,
-                                          rank, flag);
-      exclusive_scan_i32(stemp, sb, flag, excl, n, st);
-      k_scatter<<<blocks(n, T), T, 0, st>>>(n, lists[a], seg_of, seg_start_d,
-                                            flag, excl, lists2[a]);
-      std::swap(lists[a], lists2[a]);
-    }
-    k_seg_update<<<blocks(n, T), T, 0, st>>>(n, seg_start_d, seg_of);
-    FMM_HIP(hipGetLastError());
     std::vector<int32_t> nxt(2 * nseg + 1);
     for (int b = 0; b < nseg; ++b) {
-      int cnt = seg[b + 1] - seg[b];
       nxt[2 * b] = seg[b];
-      nxt[2 * b + 1] = seg[b] + (cnt + 1) / 2;
+      nxt[2 * b + 1] = seg[b] + (seg[b + 1] - seg[b] + 1) / 2;
     }
     nxt[2 * nseg] = n;
     seg.swap(nxt);
-    upload_segs();
   }
+  int32_t* segs_d = (int32_t*)sc.get(sizeof(int32_t) * all_segs.size());
+  FMM_HIP(hipMemcpyAsync(segs_d, all_segs.data(), sizeof(int32_t) * all_segs.size(),
+                         hipMemcpyHostToDevice, st));
+  for (int d = 0; d < L * s; ++d) {
+    const int nseg = 1 << d;
+    const int32_t* seg_start_d = segs_d + segs[d];
+    if (d % s == 0) {
+      int l = d / s;
+      k_geometry<<<blocks(nseg, T), T, 0, st>>>(
+          nseg, seg_start_d, list(0), list(1), list(2), X, n,
+          pl->level_off[l], pl->cx, pl->cy, pl->cz, pl->radius);
+    }
+    k_split_prep<<<blocks(nseg, T), T, 0, st>>>(nseg, seg_start_d, list(0),
+                                                list(1), list(2), X, n, rank,
+                                                axis, pivot);
+    for (int a = 0; a < 4; a += per) {
+      const dim3 g(blocks(n, T), per);
+      k_flags<<<g, T, 0, st>>>(n, list(a), seg_of, axis, pivot, rank, flag);
+      exclusive_scan_i32(stemp, sb, flag, excl, (int64_t)per * n, st);
+      k_scatter<<<g, T, 0, st>>>(n, list(a), seg_of, seg_start_d, flag, excl,
+                                 base2 + (size_t)a * n);
+    }
+    std::swap(base, base2);
+    k_seg_update<<<blocks(n, T), T, 0, st>>>(n, seg_start_d, seg_of);
+    FMM_HIP(hipGetLastError());
+  }
+  const int32_t* seg_start_d = segs_d + segs[L * s];
   const int nseg = (int)seg.size() - 1;
-  k_geometry<<<blocks(nseg, T), T, 0, st>>>(nseg, seg_start_d, lists[0],
-                                            lists[1], lists[2], X, n,
+  k_geometry<<<blocks(nseg, T), T, 0, st>>>(nseg, seg_start_d, list(0),
+                                            list(1), list(2), X, n,
                                             pl->level_off[L], pl->cx, pl->cy,
                                             pl->cz, pl->radius);
-  FMM_HIP(hipMemcpyAsync(pl->perm, lists[3], sizeof(int32_t) * n,
+  FMM_HIP(hipMemcpyAsync(pl->perm, list(3), sizeof(int32_t) * n,
                          hipMemcpyDeviceToDevice, st));
   FMM_HIP(hipMemcpyAsync(pl->leaf_start, seg_start_d,
                          sizeof(int32_t) * (nseg + 1), hipMemcpyDeviceToDevice,
                          st));
-  k_gather_pos<<<blocks(n, T), T, 0, st>>>(n, lists[3], X, pl->xs, pl->ys,
+  k_gather_pos<<<blocks(n, T), T, 0, st>>>(n, list(3), X, pl->xs, pl->ys,
                                            pl->zs);
   FMM_HIP(hipGetLastError());
   int mx = 0;
@@ -290,9 +299,9 @@ void build_tree(fmm_plan* pl, const double* pos, hipStream_t st) {
   // coincident points anywhere? (P2P then guards every pair, not only the
   // pairs inside one leaf)
   k_pos_hash<<<blocks(n, T), T, 0, st>>>(n, pl->xs, pl->ys, pl->zs, keys);
-  sort_pairs_u64_i32(temp, tb, keys, keys_out, iota, lists2[0], n, st);
+  sort_pairs_u64_i32(temp, tb, keys, keys_out, iota, base2, n, st);
   FMM_HIP(hipMemsetAsync(bad, 0, sizeof(int), st));
-  k_dup_check<<<blocks(n, T), T, 0, st>>>(n, keys_out, lists2[0], pl->xs, pl->ys, pl->zs, bad);
+  k_dup_check<<<blocks(n, T), T, 0, st>>>(n, keys_out, base2, pl->xs, pl->ys, pl->zs, bad);
   FMM_HIP(hipGetLastError());
   FMM_HIP(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, st));
   FMM_HIP(hipStreamSynchronize(st));
