@@ -372,7 +372,10 @@ fmm_status fmm_plan_autotune(fmm_plan* plan, const void* q, void* stream, int* p
 /* Launch tiles of the single-vector evaluation, as fmm_plan_autotune
  * chooses them or a caller sets them:
  *   p2p_groups       source groups of the near-field kernel: 1, 2 or 4
- *                    (2 and 4 need leaves of at most 64 / groups points)
+ *                    (2 and 4 need leaves of at most 64 / groups points).
+ *                    At the plan's default, leaves that would leave lanes
+ *                    of that kernel idle take a wider form (in FP32 with
+ *                    identical results); any other value applies to all
  *   leaves_per_wave  leaves per wave of P2M and L2P: 1, 2, 4 or 8 (at most
  *                    64 / value points per leaf)
  *   m2l_waves        waves sharing each M2L translation (Sec. II.D): 1 (one

@@ -103,6 +103,9 @@ struct NearItems {
   int32_t* split_cnt = nullptr;
   void* part = nullptr;
   int64_t n = 0, n_split = 0;
+  // items of leaves of the wide forms (near_form) come first, those of 128
+  // threads before those of 64
+  int64_t n_wide = 0, n_wide64 = 0;
 };
 
 // Interaction lists of one direction, CSR by target.  M2L work items: lane
@@ -425,6 +428,16 @@ void direct_sum(int64_t n, const double* pos, const void* q, int precision,
 // needs max_leaf_count <= 64 / G) and P2M/L2P leaves per wave (1, 2, 4, 8;
 // needs max_leaf_count <= 64 / leaves).
 int p2p_groups(const fmm_plan* pl);
+int default_p2p_groups(const fmm_plan* pl);
+// Near-field form of a target leaf of nt points with `list` source leaves in
+// `items` work items: the one with the largest share of busy lanes, the wide
+// forms' times kWideRate (their speed against k_p2p, all lanes busy).  FP64
+// leaves of a plan with two or four source groups (32 points and fewer) always
+// take the wide form; in FP32 the wide forms reproduce the sums of one source
+// group, so such plans keep k_p2p.
+enum { kNearWide = 0, kNearWide64 = 1, kNearWave = 2 };
+constexpr double kWideRate = 0.9, kWideGain = 1.08;
+int near_form(const fmm_plan* pl, int nt, int64_t list, int64_t items);
 int leaves_per_wave(const fmm_plan* pl);
 int m2l_waves(const fmm_plan* pl);
 int chain_waves(const fmm_plan* pl);

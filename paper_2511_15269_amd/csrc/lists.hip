@@ -246,41 +246,57 @@ NearItems near_items(fmm_plan* pl, const Side& T, const std::vector<int32_t>& pt
   std::vector<int32_t> il, kb, ke, sl, sf, sc;
   std::vector<int64_t> out;
   int64_t part = 0;
+  // per leaf: the runs of its list, then its form; the items are laid out
+  // form by form
+  std::vector<int32_t> cut;  // run ends of all leaves, one after another
+  std::vector<size_t> first_cut(1, 0);
+  std::vector<char> form;
   for (int64_t t = T.leaf0; t < T.leaf0 + T.nleaf; ++t) {
     const int64_t nt = ls[t + 1] - ls[t];
-    const size_t first = il.size();
     int32_t b = ptr[t];
     int64_t acc = 0;
     for (int32_t k = ptr[t]; k < ptr[t + 1]; ++k) {
       const int64_t w = nt * (int64_t)(ls[src[k] + 1] - ls[src[k]]);
       if (k > b && acc + w > budget) {
-        il.push_back((int32_t)t);
-        kb.push_back(b);
-        ke.push_back(k);
+        cut.push_back(k);
         b = k;
         acc = 0;
       }
       acc += w;
     }
-    il.push_back((int32_t)t);
-    kb.push_back(b);
-    ke.push_back(ptr[t + 1]);
-    const size_t cnt = il.size() - first;
-    if (cnt == 1) {
-      out.push_back(-1);
-      continue;
+    cut.push_back(ptr[t + 1]);
+    form.push_back((char)near_form(pl, (int)nt, ptr[t + 1] - ptr[t],
+                                   (int64_t)(cut.size() - first_cut.back())));
+    first_cut.push_back(cut.size());
+  }
+  int64_t count[3] = {0, 0, 0};
+  for (int f : {kNearWide, kNearWide64, kNearWave}) {
+    const size_t before = il.size();
+    for (int64_t i = 0; i < T.nleaf; ++i) {
+      if (form[i] != f) continue;
+      const int64_t t = T.leaf0 + i, nt = ls[t + 1] - ls[t];
+      const size_t first = il.size(), cnt = first_cut[i + 1] - first_cut[i];
+      int32_t b = ptr[t];
+      for (size_t j = first_cut[i]; j < first_cut[i + 1]; ++j) {
+        il.push_back((int32_t)t);
+        kb.push_back(b);
+        ke.push_back(cut[j]);
+        b = cut[j];
+        out.push_back(cnt == 1 ? -1 : part);
+        if (cnt > 1) part += 4 * nt;
+      }
+      if (cnt == 1) continue;
+      sl.push_back((int32_t)t);
+      sf.push_back((int32_t)first);
+      sc.push_back((int32_t)cnt);
     }
-    for (size_t j = 0; j < cnt; ++j) {
-      out.push_back(part);
-      part += 4 * nt;
-    }
-    sl.push_back((int32_t)t);
-    sf.push_back((int32_t)first);
-    sc.push_back((int32_t)cnt);
+    count[f] = (int64_t)(il.size() - before);
   }
   NearItems N;
   N.n = (int64_t)il.size();
   N.n_split = (int64_t)sl.size();
+  N.n_wide = count[kNearWide];
+  N.n_wide64 = count[kNearWide64];
   Upload up;
   up.add(il, &N.leaf);
   up.add(kb, &N.kb);

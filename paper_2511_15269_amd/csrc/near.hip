@@ -12,7 +12,9 @@ namespace {
 using namespace ops;
 
 // One source point against the lane's target at (xi, yi, zi): the
-// difference is taken in FP64 and rounded to T.  SAFE: pairs at distance 0
+// difference is taken in FP64 and rounded to T.  In FP64 the Newton step
+// gives 2 / r, one operation less than 1 / r (near_scale takes the powers of
+// two out again: 17 instead of 18 operations).  SAFE: pairs at distance 0
 // contribute nothing (needed within a leaf, and between leaves when the
 // point set has coincident points); otherwise the pair is known to be apart.
 template <typename T, bool FIELD, bool SAFE>
@@ -20,7 +22,7 @@ __device__ __forceinline__ void p2p_pair(const Src<T>& s, double xi, double yi, 
                                          T& u, T& gx, T& gy, T& gz) {
   const T dx = T(xi - s.x), dy = T(yi - s.y), dz = T(zi - s.z);
   const T r2 = dx * dx + dy * dy + dz * dz;
-  const T inv0 = inv_sqrt(r2);
+  const T inv0 = inv_sqrt2(r2);
   const T inv = SAFE ? (r2 > T(0) ? inv0 : T(0)) : inv0;
   const T qi = s.q * inv;
   u += qi;
@@ -30,6 +32,13 @@ __device__ __forceinline__ void p2p_pair(const Src<T>& s, double xi, double yi, 
     gy = fma(q3, dy, gy);
     gz = fma(q3, dz, gz);
   }
+}
+
+// Factor of the near field's sums: -1/(4 pi), and 1/2 or 1/8 for the factor
+// of inv_sqrt2 in the potential and the field.
+template <typename T>
+__device__ __forceinline__ constexpr T near_scale(bool field) {
+  return sizeof(T) == 4 ? -T(kInv4Pi) : -T(kInv4Pi) * T(field ? 0.125 : 0.5);
 }
 
 constexpr int kChunk = 8;
@@ -53,10 +62,10 @@ constexpr int kChunk = 8;
 // combined with cross-lane shuffles in a fixed order.
 template <typename T, bool FIELD, int G>
 __global__ __launch_bounds__(64) void k_p2p(
-    int64_t n, const int32_t* __restrict__ item_leaf, const int32_t* __restrict__ item_kb,
-    const int32_t* __restrict__ item_ke, const int64_t* __restrict__ item_out,
-    const int32_t* __restrict__ leaf_start, const double* __restrict__ xs,
-    const double* __restrict__ ys, const double* __restrict__ zs,
+    int64_t n, int item0, const int32_t* __restrict__ item_leaf,
+    const int32_t* __restrict__ item_kb, const int32_t* __restrict__ item_ke,
+    const int64_t* __restrict__ item_out, const int32_t* __restrict__ leaf_start,
+    const double* __restrict__ xs, const double* __restrict__ ys, const double* __restrict__ zs,
     const Src<T>* __restrict__ src, const int32_t* __restrict__ p2p_src, int dup,
     T* __restrict__ near, T* __restrict__ part) {
   constexpr int TL = 64 / G;  // targets per pass
@@ -67,7 +76,7 @@ __global__ __launch_bounds__(64) void k_p2p(
   // neighbouring target leaves share most source leaves, so their records
   // stay in one XCD's L2, while leaves of unequal cost (several problems,
   // clustered points) spread over all XCDs
-  const int item = (int)xcd_chunked<64>(blockIdx.x, gridDim.x);
+  const int item = item0 + (int)xcd_chunked<64>(blockIdx.x, gridDim.x);
   const int leaf = item_leaf[item];
   const int lane = threadIdx.x;
   const int g = G == 1 ? 0 : lane / TL;
@@ -152,23 +161,332 @@ __global__ __launch_bounds__(64) void k_p2p(
     if (live && g == 0) {
       // field = -grad u;  grad of the near part is +(1/4pi) sum q d/r^3
       if (po < 0) {  // the leaf's only item: its near field
-        near[i] = -T(kInv4Pi) * u;
+        near[i] = near_scale<T>(false) * u;
         if (FIELD) {
           T* f = near + n + 3 * (int64_t)i;
-          f[0] = -T(kInv4Pi) * gx;
-          f[1] = -T(kInv4Pi) * gy;
-          f[2] = -T(kInv4Pi) * gz;
+          f[0] = near_scale<T>(true) * gx;
+          f[1] = near_scale<T>(true) * gy;
+          f[2] = near_scale<T>(true) * gz;
         }
       } else {  // one of several items of the leaf: rows of its partial sums
         const int nt = en - st, li = i - st;
         T* r = part + po;
-        r[li] = -T(kInv4Pi) * u;
+        r[li] = near_scale<T>(false) * u;
         if (FIELD) {
-          r[nt + li] = -T(kInv4Pi) * gx;
-          r[2 * nt + li] = -T(kInv4Pi) * gy;
-          r[3 * nt + li] = -T(kInv4Pi) * gz;
+          r[nt + li] = near_scale<T>(true) * gx;
+          r[2 * nt + li] = near_scale<T>(true) * gy;
+          r[3 * nt + li] = near_scale<T>(true) * gz;
         }
       }
+    }
+  }
+}
+
+// The same items with every lane at work (FP32): a thread holds two targets
+// (i and i + h of the leaf's nt, h = nt / 2 rounded up) and the W / h groups
+// of h threads each take another source leaf of the item's list.  A group's threads sum their leaf's points in order, as k_p2p does;
+// the leaf sums then pass through LDS to the thread that keeps the running
+// sum of a (component, target) pair, which adds them in list order (Neumaier
+// in FP32): the results are those of k_p2p with one source group, bit for
+// bit.  Lanes stay idle only for the remainders of W / h and of the
+// list over the groups, against 64 - nt mod 64 lanes of every wave in k_p2p; a record read from LDS (32
+// bytes a lane, the same for a group) serves two pairs, since one pair per
+// read keeps the LDS as busy as the VALU.  Bound by VALU issue.
+// Measured (near
+// field, FP32): 200003 Plummer points, 49 a leaf, 3.42 -> 3.12 ms; 16 problems
+// of 16 to 122 points a leaf 1.61 -> 1.37 ms.
+template <bool FIELD, int W>
+__global__ __launch_bounds__(W) __attribute__((amdgpu_waves_per_eu(4))) void k_p2p_wide(
+    int64_t n, int item0, const int32_t* __restrict__ item_leaf,
+    const int32_t* __restrict__ item_kb, const int32_t* __restrict__ item_ke,
+    const int64_t* __restrict__ item_out, const int32_t* __restrict__ leaf_start,
+    const double* __restrict__ xs, const double* __restrict__ ys, const double* __restrict__ zs,
+    const Src<float>* __restrict__ src, const int32_t* __restrict__ p2p_src, int dup,
+    float* __restrict__ near, float* __restrict__ part) {
+  typedef float T;
+  constexpr int NC = FIELD ? 4 : 1;
+  constexpr int kWideTargets = W;     // targets at a time (two groups or more)
+  constexpr int kWideStage = 2 * W;   // staged source records (all groups)
+  constexpr int NQ = NC;              // running sums per thread
+  constexpr int U = 4;                // records in registers
+  __shared__ __align__(32) double2 stage[2 * kWideStage];
+  __shared__ T sums[2 * NC][W];
+  __shared__ int ljs[W], lcnt[W];  // source leaves: first point, count
+  __shared__ int lmax[2], lself[2];
+  const int item = item0 + (int)xcd_chunked<64>(blockIdx.x, gridDim.x);
+  const int tid = threadIdx.x;
+  const int leaf = item_leaf[item];
+  const int st = leaf_start[leaf], nt = leaf_start[leaf + 1] - st;
+  const int pb = item_kb[item], pe = item_ke[item];
+  const int64_t po = item_out[item];
+  const double2* words = reinterpret_cast<const double2*>(src);
+  for (int t0 = 0; t0 < nt; t0 += kWideTargets) {
+    const int ntt = min(kWideTargets, nt - t0);
+    const int h = (ntt + 1) / 2, ng = W / h;  // threads per group, groups
+    const int CS = kWideStage / ng;               // staged points per group
+    const int g = tid / h, i = tid - g * h;
+    const int ia = st + t0 + min(i, ntt - 1), ib = st + t0 + min(i + h, ntt - 1);
+    const double xa = xs[ia], ya = ys[ia], za = zs[ia];
+    const double xb = xs[ib], yb = ys[ib], zb = zs[ib];
+    // record that this thread stages (the second one W / CS groups on)
+    const int g0 = tid / CS, r0 = tid - g0 * CS;
+    const int g1 = (tid + W) / CS, r1 = tid + W - g1 * CS;
+    // running sums q = tid + W m of (component q / ntt, target q % ntt)
+    T s[NQ], c[NQ];
+    int at[NQ];
+#pragma unroll
+    for (int m = 0; m < NQ; ++m) {
+      const int q = tid + W * m, comp = q / ntt, t = q - comp * ntt;
+      s[m] = c[m] = T(0);
+      at[m] = q < NC * ntt ? (t < h ? comp * W + t : (NC + comp) * W + t - h) : -1;
+    }
+    for (int kb = pb; kb < pe; kb += W) {
+      const int nk = min(W, pe - kb);
+      __syncthreads();  // the previous leaves' entries and sums are done with
+      {
+        const int sl = p2p_src[kb + min(tid, nk - 1)];
+        const int js = leaf_start[sl], cnt = leaf_start[sl + 1] - js;
+        ljs[tid] = js;
+        lcnt[tid] = cnt;
+        // largest leaf and the target leaf's own place (-1: not here)
+        int mx = cnt, self = sl == leaf ? min(tid, nk - 1) : -1;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+          mx = max(mx, __shfl_xor(mx, off, 64));
+          self = max(self, __shfl_xor(self, off, 64));
+        }
+        lmax[tid / 64] = mx;
+        lself[tid / 64] = self;
+      }
+      __syncthreads();
+      const int most = __builtin_amdgcn_readfirstlane(max(lmax[0], lmax[W / 64 - 1]));
+      const int self = __builtin_amdgcn_readfirstlane(max(lself[0], lself[W / 64 - 1]));
+      for (int k0 = 0; k0 < nk; k0 += ng) {
+        const int kn = min(ng, nk - k0);
+        const bool mine = g < kn;
+        T ua = T(0), xa_ = T(0), ya_ = T(0), za_ = T(0), ub = T(0), xb_ = T(0), yb_ = T(0),
+          zb_ = T(0);
+        const bool safe = dup || (self >= k0 && self < k0 + kn);
+        for (int c0 = 0; c0 < most; c0 += CS) {
+          __syncthreads();  // the staged records and the leaf sums are done with
+          if (g0 < kn && c0 + r0 < lcnt[k0 + g0]) {
+            const int64_t j = 2 * ((int64_t)ljs[k0 + g0] + c0 + r0);
+            const double2 w0 = words[j], w1 = words[j + 1];
+            stage[2 * tid] = w0;
+            stage[2 * tid + 1] = w1;
+          }
+          if (g1 < kn && c0 + r1 < lcnt[k0 + g1]) {
+            const int64_t j = 2 * ((int64_t)ljs[k0 + g1] + c0 + r1);
+            const double2 w0 = words[j], w1 = words[j + 1];
+            stage[2 * (tid + W)] = w0;
+            stage[2 * (tid + W) + 1] = w1;
+          }
+          __syncthreads();
+          const int cnt = mine ? min(CS, lcnt[k0 + g] - c0) : 0;
+          const Src<T>* rec = reinterpret_cast<const Src<T>*>(stage) + (mine ? g * CS : 0);
+          auto sweep = [&](auto safe_tag) {
+            constexpr bool S = decltype(safe_tag)::value;
+            int e = 0;
+            for (; e + U <= cnt; e += U) {
+              Src<T> r[U];
+#pragma unroll
+              for (int t = 0; t < U; ++t) r[t] = rec[e + t];
+#pragma unroll
+              for (int t = 0; t < U; ++t) {
+                p2p_pair<T, FIELD, S>(r[t], xa, ya, za, ua, xa_, ya_, za_);
+                p2p_pair<T, FIELD, S>(r[t], xb, yb, zb, ub, xb_, yb_, zb_);
+              }
+            }
+            for (; e < cnt; ++e) {
+              const Src<T> r = rec[e];
+              p2p_pair<T, FIELD, S>(r, xa, ya, za, ua, xa_, ya_, za_);
+              p2p_pair<T, FIELD, S>(r, xb, yb, zb, ub, xb_, yb_, zb_);
+            }
+          };
+          if (safe)
+            sweep(std::true_type{});
+          else
+            sweep(std::false_type{});
+        }
+        {  // leaf sums (the last round's merge ended before a barrier)
+          sums[0][tid] = ua;
+          sums[NC][tid] = ub;
+          if constexpr (FIELD) {
+            sums[1][tid] = xa_;
+            sums[2][tid] = ya_;
+            sums[3][tid] = za_;
+            sums[NC + 1][tid] = xb_;
+            sums[NC + 2][tid] = yb_;
+            sums[NC + 3][tid] = zb_;
+          }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < NQ; ++m) {
+          if (at[m] < 0) continue;
+          const T* x = &sums[0][0] + at[m];
+          for (int gg = 0; gg < kn; ++gg) neumaier(s[m], c[m], x[gg * h]);
+        }
+      }
+    }
+    const T su = near_scale<T>(false), sg = near_scale<T>(true);
+#pragma unroll
+    for (int m = 0; m < NQ; ++m) {
+      if (at[m] < 0) continue;
+      const int q = tid + W * m, comp = q / ntt, li = t0 + q - comp * ntt;
+      const T v = (comp == 0 ? su : sg) * (s[m] + c[m]);
+      if (po >= 0)
+        part[po + (int64_t)comp * nt + li] = v;
+      else if (comp == 0)
+        near[st + li] = v;
+      else
+        near[n + 3 * (int64_t)(st + li) + comp - 1] = v;
+    }
+  }
+}
+
+// FP64, where the order of the sums is free: the same threads and targets,
+// but the groups share out the points of the item's source leaves (staged
+// one after another, group g takes every ng-th record) and every thread sums
+// all its points before the groups' sums are added once, so that neither
+// leaves nor lists leave groups idle.  Bound by VALU issue (17 FP64
+// operations and the reciprocal square root a pair).  Measured (near field
+// against k_p2p with two or four groups): 384 charges and 2048 probes 33 ->
+// 13 us, uniform cube 2^20 (32 points a leaf) 0.64 -> 0.63 ms.
+template <bool FIELD, int W>
+__global__ __launch_bounds__(W) __attribute__((amdgpu_waves_per_eu(4))) void k_p2p_flat(
+    int64_t n, int item0, const int32_t* __restrict__ item_leaf,
+    const int32_t* __restrict__ item_kb, const int32_t* __restrict__ item_ke,
+    const int64_t* __restrict__ item_out, const int32_t* __restrict__ leaf_start,
+    const double* __restrict__ xs, const double* __restrict__ ys, const double* __restrict__ zs,
+    const Src<double>* __restrict__ src, const int32_t* __restrict__ p2p_src, int dup,
+    double* __restrict__ near, double* __restrict__ part) {
+  constexpr int NC = FIELD ? 4 : 1;
+  constexpr int U = 4;              // records in registers
+  constexpr int kFlatStage = 2 * W;  // staged source records
+  // the staged records, and in the end the threads' sums [2 NC][W]
+  __shared__ __align__(32) double2 stage[2 * kFlatStage];
+  static_assert(2 * NC * W * sizeof(double) <= sizeof(stage), "sums fit the stage");
+  __shared__ int ljs[W], lcnt[W];  // source leaves: first point, count
+  __shared__ int lpos[W + 1];          // points of the leaves before
+  __shared__ int lmax[2], lself[2];
+  const int item = item0 + (int)xcd_chunked<64>(blockIdx.x, gridDim.x);
+  const int tid = threadIdx.x;
+  const int leaf = item_leaf[item];
+  const int st = leaf_start[leaf], nt = leaf_start[leaf + 1] - st;
+  const int pb = item_kb[item], pe = item_ke[item];
+  const int64_t po = item_out[item];
+  const double2* words = reinterpret_cast<const double2*>(src);
+  for (int t0 = 0; t0 < nt; t0 += 2 * W) {
+    const int ntt = min(2 * W, nt - t0);
+    const int h = (ntt + 1) / 2, ng = W / h;  // threads per group, groups
+    const int g = tid / h, i = tid - g * h;
+    const bool mine = g < ng;
+    const int ia = st + t0 + min(i, ntt - 1), ib = st + t0 + min(i + h, ntt - 1);
+    const double xa = xs[ia], ya = ys[ia], za = zs[ia];
+    const double xb = xs[ib], yb = ys[ib], zb = zs[ib];
+    double a[4] = {0.0, 0.0, 0.0, 0.0}, b[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int kb = pb; kb < pe; kb += W) {
+      const int nk = min(W, pe - kb);
+      __syncthreads();  // the previous leaves' entries are done with
+      {
+        const int sl = p2p_src[kb + min(tid, nk - 1)];
+        const int js = leaf_start[sl], cnt = tid < nk ? leaf_start[sl + 1] - js : 0;
+        ljs[tid] = js;
+        lcnt[tid] = cnt;
+        // largest leaf, the target leaf's own place (-1: not here), and the
+        // points before each leaf
+        int mx = cnt, self = tid < nk && sl == leaf ? tid : -1, sum = cnt;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+          mx = max(mx, __shfl_xor(mx, off, 64));
+          self = max(self, __shfl_xor(self, off, 64));
+          const int left = __shfl_up(sum, off, 64);
+          if (tid % 64 >= off) sum += left;
+        }
+        lmax[tid / 64] = mx;
+        lself[tid / 64] = self;
+        if (tid == 63) lpos[64] = sum;
+        if (tid < 64) lpos[tid] = sum - cnt;
+        if (W > 64) {
+          __syncthreads();
+          if (tid >= 64) lpos[tid + 1] = lpos[64] + sum;
+        }
+      }
+      __syncthreads();
+      const int most = __builtin_amdgcn_readfirstlane(max(lmax[0], lmax[W / 64 - 1]));
+      const int self = __builtin_amdgcn_readfirstlane(max(lself[0], lself[W / 64 - 1]));
+      const int nl = max(kFlatStage / most, 1);  // leaves staged at a time
+      const int inv = (1 << 16) / most + 1;      // e / most = e inv >> 16 for e < kFlatStage
+      for (int k0 = 0; k0 < nk; k0 += nl) {
+        const int kn = min(nl, nk - k0);
+        const bool safe = dup || (self >= k0 && self < k0 + kn);
+        // leaves of more than kFlatStage points come in pieces
+        for (int c0 = 0; c0 < most; c0 += kFlatStage) {
+          const int p0 = lpos[k0];
+          const int tot = nl > 1 ? lpos[k0 + kn] - p0 : min(kFlatStage, lcnt[k0] - c0);
+          __syncthreads();  // the staged records are done with
+#pragma unroll
+          for (int u = 0; u < kFlatStage / W; ++u) {
+            const int e = tid + u * W;
+            const int l = nl > 1 ? e * inv >> 16 : 0, r = nl > 1 ? e - l * most : c0 + e;
+            if (l < kn && r < lcnt[k0 + l]) {
+              const int64_t j = 2 * ((int64_t)ljs[k0 + l] + r);
+              const double2 w0 = words[j], w1 = words[j + 1];
+              const int to = nl > 1 ? lpos[k0 + l] - p0 + r : e;
+              stage[2 * to] = w0;
+              stage[2 * to + 1] = w1;
+            }
+          }
+          __syncthreads();
+          const Src<double>* rec = reinterpret_cast<const Src<double>*>(stage) + (mine ? g : 0);
+          const int full = tot / ng;  // records of every group
+          auto sweep = [&](auto safe_tag) {
+            constexpr bool S = decltype(safe_tag)::value;
+            auto both = [&](const Src<double>& r) {
+              p2p_pair<double, FIELD, S>(r, xa, ya, za, a[0], a[1], a[2], a[3]);
+              p2p_pair<double, FIELD, S>(r, xb, yb, zb, b[0], b[1], b[2], b[3]);
+            };
+            int e = 0;
+            for (; e + U <= full; e += U) {
+              Src<double> r[U];
+#pragma unroll
+              for (int t = 0; t < U; ++t) r[t] = rec[(e + t) * ng];
+#pragma unroll
+              for (int t = 0; t < U; ++t) both(r[t]);
+            }
+            for (; e < full; ++e) both(rec[e * ng]);
+            if (mine && g < tot - full * ng) both(rec[full * ng]);
+          };
+          if (safe)
+            sweep(std::true_type{});
+          else
+            sweep(std::false_type{});
+        }
+      }
+    }
+    // the groups' sums added in group order
+    double* sums = reinterpret_cast<double*>(stage);
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      sums[c * W + tid] = a[c];
+      sums[(NC + c) * W + tid] = b[c];
+    }
+    __syncthreads();
+    for (int q = tid; q < NC * ntt; q += W) {
+      const int comp = q / ntt, t = q - comp * ntt;
+      const double* x = sums + (t < h ? comp * W + t : (NC + comp) * W + t - h);
+      double v = 0.0;
+      for (int gg = 0; gg < ng; ++gg) v += x[gg * h];
+      v *= near_scale<double>(comp > 0);
+      const int li = t0 + t;
+      if (po >= 0)
+        part[po + (int64_t)comp * nt + li] = v;
+      else if (comp == 0)
+        near[st + li] = v;
+      else
+        near[n + 3 * (int64_t)(st + li) + comp - 1] = v;
     }
   }
 }
@@ -226,22 +544,34 @@ __global__ __launch_bounds__(64) void k_p2p_sum(
 template <typename T>
 void run_near(fmm_plan* pl, const ListSet& Ls, const Src<T>* src, int64_t n, T* near, bool field,
               hipStream_t sp) {
-  const int G = p2p_groups(pl);
   const NearItems& N = Ls.near;
-  auto p2p = [&](auto kern) {
-    kern<<<(unsigned)N.n, 64, 0, sp>>>(n, N.leaf, N.kb, N.ke, N.out, pl->leaf_start, pl->xs,
-                                       pl->ys, pl->zs, src, Ls.p2p_src, pl->has_dup ? 1 : 0, near,
-                                       (T*)N.part);
+  const int G = p2p_groups(pl);
+  // items [first, first + count) on kern, `threads` a block
+  auto launch = [&](auto kern, int threads, int64_t first, int64_t count) {
+    if (count == 0) return;
+    kern<<<(unsigned)count, threads, 0, sp>>>(n, (int)first, N.leaf, N.kb, N.ke, N.out,
+                                              pl->leaf_start, pl->xs, pl->ys, pl->zs, src,
+                                              Ls.p2p_src, pl->has_dup ? 1 : 0, near, (T*)N.part);
   };
-  if (field) {
-    if (G == 1) p2p(k_p2p<T, true, 1>);
-    else if (G == 2) p2p(k_p2p<T, true, 2>);
-    else p2p(k_p2p<T, true, 4>);
-  } else {
-    if (G == 1) p2p(k_p2p<T, false, 1>);
-    else if (G == 2) p2p(k_p2p<T, false, 2>);
-    else p2p(k_p2p<T, false, 4>);
-  }
+  // the wide forms take the leaves they were given (near_form) unless another
+  // number of source groups than the plan's own is asked for
+  const bool own = G == default_p2p_groups(pl);
+  const int64_t w0 = own ? N.n_wide : 0, w1 = own ? N.n_wide64 : 0, rest = w0 + w1;
+  auto all = [&](auto field_tag) {
+    constexpr bool F = decltype(field_tag)::value;
+    if constexpr (sizeof(T) == 8) {
+      launch(k_p2p_flat<F, 128>, 128, 0, w0);
+      launch(k_p2p_flat<F, 64>, 64, w0, w1);
+    } else {
+      launch(k_p2p_wide<F, 128>, 128, 0, w0);
+      launch(k_p2p_wide<F, 64>, 64, w0, w1);
+    }
+    if (G == 1) launch(k_p2p<T, F, 1>, 64, rest, N.n - rest);
+    else if (G == 2) launch(k_p2p<T, F, 2>, 64, rest, N.n - rest);
+    else launch(k_p2p<T, F, 4>, 64, rest, N.n - rest);
+  };
+  if (field) all(std::true_type{});
+  else all(std::false_type{});
   if (N.n_split > 0) {
     auto sum = [&](auto kern) {
       // a block per 64 columns of the largest leaf (others loop or idle)

@@ -638,12 +638,13 @@ __device__ __forceinline__ void local_eval_grad(T x, T y, T z, const T* __restri
 
 
 // ---------------------------------------------------------------- P2P
-__device__ __forceinline__ double inv_sqrt(double r2) {
-  // hardware estimate refined by one Newton step
+// FP64: 2 / sqrt(r2), the hardware estimate y refined by one Newton step,
+// y (3 - r2 y^2); FP32: 1 / sqrt(r2), the hardware's.
+__device__ __forceinline__ double inv_sqrt2(double r2) {
   const double y = __builtin_amdgcn_rsq(r2);
-  return y * fma(-0.5 * r2, y * y, 1.5);
+  return y * fma(-(r2 * y), y, 3.0);
 }
-__device__ __forceinline__ float inv_sqrt(float r2) { return __builtin_amdgcn_rsqf(r2); }
+__device__ __forceinline__ float inv_sqrt2(float r2) { return __builtin_amdgcn_rsqf(r2); }
 
 // ------------------------------------------------------ block placement
 // Workgroups are handed to the 8 XCDs round robin (block b to XCD b % 8),

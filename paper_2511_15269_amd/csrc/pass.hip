@@ -1,5 +1,7 @@
 // One evaluation pass of a plan: the launch tiles in effect, the choice of
 // the order's kernels (eval.hip) and the adjoint's combine step.
+#include <cmath>
+
 #include "internal.h"
 
 namespace fmm {
@@ -10,10 +12,36 @@ bool valid_p2p_groups(const fmm_plan* pl, int g) {
 bool valid_leaves_per_wave(const fmm_plan* pl, int l) {
   return l == 1 || ((l == 2 || l == 4 || l == 8) && pl->max_leaf_count <= 64 / l);
 }
-int p2p_groups(const fmm_plan* pl) {
-  if (pl->p2p_groups && valid_p2p_groups(pl, pl->p2p_groups)) return pl->p2p_groups;
+int default_p2p_groups(const fmm_plan* pl) {
   const int m = pl->max_leaf_count;
   return m > 32 ? 1 : (m > 16 ? 2 : 4);
+}
+int p2p_groups(const fmm_plan* pl) {
+  if (pl->p2p_groups && valid_p2p_groups(pl, pl->p2p_groups)) return pl->p2p_groups;
+  return default_p2p_groups(pl);
+}
+int near_form(const fmm_plan* pl, int nt, int64_t list, int64_t items) {
+  const bool fp64 = pl->prm.precision == FMM_FP64;
+  if (!fp64 && default_p2p_groups(pl) > 1) return kNearWave;
+  const int h = (nt + 1) / 2;
+  const double wave = fp64 && default_p2p_groups(pl) > 1 ? 0.0 : nt / (64.0 * ((nt + 63) / 64));
+  const double len = (double)list / (double)items;  // source leaves of an item
+  int form = kNearWave;
+  double best = wave;
+  for (int W : {64, 128}) {
+    // targets at a time: two a thread, in FP32 no fewer than two groups
+    if (nt > (fp64 ? 2 * W : W)) continue;
+    const int ng = W / h;
+    // share of busy lanes; in FP32 the list's leaves go to the groups in rounds
+    const double rounds = fp64 ? len / ng : std::ceil(len / ng);
+    const double rate = kWideRate * nt * len / (2.0 * W * rounds);
+    // the larger block has to be worth its barriers and its set-up
+    if (rate > (form == kNearWide64 ? kWideGain * best : best)) {
+      best = rate;
+      form = W == 128 ? kNearWide : kNearWide64;
+    }
+  }
+  return form;
 }
 int chain_waves(const fmm_plan* pl) {
   return pl->prm.p < kChainShareMinOrder || pl->chain_waves == 1 ? 1 : kShareWaves;
