@@ -184,17 +184,17 @@ __global__ __launch_bounds__(64) void k_p2p(
 
 // The same items with every lane at work (FP32): a thread holds two targets
 // (i and i + h of the leaf's nt, h = nt / 2 rounded up) and the W / h groups
-// of h threads each take another source leaf of the item's list.  A group's threads sum their leaf's points in order, as k_p2p does;
-// the leaf sums then pass through LDS to the thread that keeps the running
-// sum of a (component, target) pair, which adds them in list order (Neumaier
-// in FP32): the results are those of k_p2p with one source group, bit for
-// bit.  Lanes stay idle only for the remainders of W / h and of the
-// list over the groups, against 64 - nt mod 64 lanes of every wave in k_p2p; a record read from LDS (32
-// bytes a lane, the same for a group) serves two pairs, since one pair per
-// read keeps the LDS as busy as the VALU.  Bound by VALU issue.
-// Measured (near
-// field, FP32): 200003 Plummer points, 49 a leaf, 3.42 -> 3.12 ms; 16 problems
-// of 16 to 122 points a leaf 1.61 -> 1.37 ms.
+// of h threads each take another source leaf of the item's list.  A group's
+// threads sum their leaf's points in order, as k_p2p does; the leaf sums then
+// pass through LDS to the thread that keeps the running sum of a (component,
+// target) pair, which adds them in list order (Neumaier): the results are
+// those of k_p2p with one source group, bit for bit.  Lanes stay idle only
+// for the remainders of W / h and of the list over the groups, against 64 -
+// nt mod 64 lanes of every wave in k_p2p; a record read from LDS (32 bytes a
+// lane, the same for a group) serves two pairs, since one pair per read keeps
+// the LDS as busy as the VALU.  Bound by VALU issue.  Measured (near field,
+// FP32): 200003 Plummer points, 49 a leaf, 3.42 -> 3.12 ms; 16 problems of 16
+// to 122 points a leaf 1.61 -> 1.37 ms.
 template <bool FIELD, int W>
 __global__ __launch_bounds__(W) __attribute__((amdgpu_waves_per_eu(4))) void k_p2p_wide(
     int64_t n, int item0, const int32_t* __restrict__ item_leaf,
