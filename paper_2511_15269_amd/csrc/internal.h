@@ -103,9 +103,11 @@ struct NearItems {
   int32_t* split_cnt = nullptr;
   void* part = nullptr;
   int64_t n = 0, n_split = 0;
-  // items of leaves of the wide forms (near_form) come first, those of 128
-  // threads before those of 64
-  int64_t n_wide = 0, n_wide64 = 0;
+  // items of leaves of the wide forms (near_form) come first, those of more
+  // threads (256, 128, 64) before those of fewer
+  int64_t n_wide256 = 0, n_wide = 0, n_wide64 = 0;
+  // form of the remaining items in passes without a field (near_form)
+  int rest_pot = 0;
 };
 
 // Interaction lists of one direction, CSR by target.  M2L work items: lane
@@ -429,15 +431,36 @@ void direct_sum(int64_t n, const double* pos, const void* q, int precision,
 // needs max_leaf_count <= 64 / leaves).
 int p2p_groups(const fmm_plan* pl);
 int default_p2p_groups(const fmm_plan* pl);
-// Near-field form of a target leaf of nt points with `list` source leaves in
-// `items` work items: the one with the largest share of busy lanes, the wide
-// forms' times kWideRate (their speed against k_p2p, all lanes busy).  FP64
-// leaves of a plan with two or four source groups (32 points and fewer) always
-// take the wide form; in FP32 the wide forms reproduce the sums of one source
-// group, so such plans keep k_p2p.
-enum { kNearWide = 0, kNearWide64 = 1, kNearWave = 2 };
-constexpr double kWideRate = 0.9, kWideGain = 1.08;
-int near_form(const fmm_plan* pl, int nt, int64_t list, int64_t items);
+// Near-field form of the target leaves of nt points, whose direct lists have
+// `list` source leaves per work item on average, in a plan of `items` items:
+// the largest product of
+//   - the share of busy lanes (of the waves that have work: a round of the
+//     list that leaves whole waves without a leaf costs nothing),
+//   - the form's rate with all lanes busy against k_p2p's, and
+//   - x / (x + 1) for x waves per SIMD (1024 SIMDs), the fill of the chip.
+// The rates are those measured on cubes of 2^12 leaves of 16 to 250 points
+// (FP32); a pass without a field has the higher ones, since a pair is cheaper
+// there and a record's read is shared by two.  The product then orders the
+// forms as measured from 2^6 leaves on, e.g. (pass in us, one wave | 64 | 128
+// | 256 threads): 2^8 leaves of 56 points 129 | 103 | 85 | 84, of 150 220 | -
+// | - | 215; 2^12 leaves of 48 366 | 349 | 305 | 305, of 72 825 | - | 577 |
+// 571, of 112 1103 | - | 1196 | 1292; potential of 2^12 leaves of 56 312 |
+// 287 | 295 | 303, of 104 847 | - | 802 | 900.  256 threads serve to fill the
+// chip only: with 16 waves a SIMD and more they gain 0 to 4% by themselves
+// (9% for 132 to 140 points) but hold up the far field beside them (16
+// problems of 22 to 109 points a leaf, pass: 1.65 | 1.76 ms without and with).
+// FP64 leaves of a plan with two or four source groups (32 points and fewer)
+// always take the wide form; in FP32 the wide forms reproduce the sums of one
+// source group, so such plans keep k_p2p.
+enum { kNearWide256 = 0, kNearWide = 1, kNearWide64 = 2, kNearWave = 3 };
+struct WideRates {
+  double w64, w128, w256;
+};
+constexpr WideRates kWideField{1.0, 0.97, 0.88}, kWidePot{1.12, 1.05, 0.95};
+constexpr double kWideFillWaves = 16.0;
+// FP64: the flat form's rate, and what 128 threads have to gain on 64
+constexpr double kFlatRate = 0.9, kFlatGain = 1.08;
+int near_form(const fmm_plan* pl, int nt, double list, int64_t items, bool field);
 int leaves_per_wave(const fmm_plan* pl);
 int m2l_waves(const fmm_plan* pl);
 int chain_waves(const fmm_plan* pl);

@@ -23,6 +23,7 @@
 #pragma clang fp contract(off)
 
 #include <algorithm>
+#include <map>
 #include <climits>
 #include <cmath>
 
@@ -246,11 +247,11 @@ NearItems near_items(fmm_plan* pl, const Side& T, const std::vector<int32_t>& pt
   std::vector<int32_t> il, kb, ke, sl, sf, sc;
   std::vector<int64_t> out;
   int64_t part = 0;
-  // per leaf: the runs of its list, then its form; the items are laid out
-  // form by form
+  // the runs of every leaf's list, then the forms; the items are laid out form
+  // by form
   std::vector<int32_t> cut;  // run ends of all leaves, one after another
   std::vector<size_t> first_cut(1, 0);
-  std::vector<char> form;
+  std::map<int64_t, std::pair<int64_t, int64_t>> per_size;  // leaf size: list, items
   for (int64_t t = T.leaf0; t < T.leaf0 + T.nleaf; ++t) {
     const int64_t nt = ls[t + 1] - ls[t];
     int32_t b = ptr[t];
@@ -265,16 +266,24 @@ NearItems near_items(fmm_plan* pl, const Side& T, const std::vector<int32_t>& pt
       acc += w;
     }
     cut.push_back(ptr[t + 1]);
-    form.push_back((char)near_form(pl, (int)nt, ptr[t + 1] - ptr[t],
-                                   (int64_t)(cut.size() - first_cut.back())));
+    per_size[nt].first += ptr[t + 1] - ptr[t];
+    per_size[nt].second += (int64_t)(cut.size() - first_cut.back());
     first_cut.push_back(cut.size());
   }
-  int64_t count[3] = {0, 0, 0};
-  for (int f : {kNearWide, kNearWide64, kNearWave}) {
+  // one form for all leaves of a size (each form is a launch of its own)
+  std::map<int64_t, int> form_of;
+  for (const auto& [nt, sum] : per_size)
+    form_of[nt] = near_form(pl, (int)nt, (double)sum.first / (double)sum.second,
+                            (int64_t)cut.size(), true);
+  std::vector<char> form(T.nleaf);
+  for (int64_t i = 0; i < T.nleaf; ++i)
+    form[i] = (char)form_of[ls[T.leaf0 + i + 1] - ls[T.leaf0 + i]];
+  int64_t count[4] = {0, 0, 0, 0};
+  for (int f : {kNearWide256, kNearWide, kNearWide64, kNearWave}) {
     const size_t before = il.size();
     for (int64_t i = 0; i < T.nleaf; ++i) {
-      if (form[i] != f) continue;
       const int64_t t = T.leaf0 + i, nt = ls[t + 1] - ls[t];
+      if (form[i] != f) continue;
       const size_t first = il.size(), cnt = first_cut[i + 1] - first_cut[i];
       int32_t b = ptr[t];
       for (size_t j = first_cut[i]; j < first_cut[i + 1]; ++j) {
@@ -295,6 +304,18 @@ NearItems near_items(fmm_plan* pl, const Side& T, const std::vector<int32_t>& pt
   NearItems N;
   N.n = (int64_t)il.size();
   N.n_split = (int64_t)sl.size();
+  N.rest_pot = kNearWave;
+  if (count[kNearWave] > 0) {  // by the items' mean leaf size and list
+    double points = 0.0, list = 0.0;
+    for (const auto& [nt, sum] : per_size)
+      if (form_of[nt] == kNearWave) {
+        points += (double)nt * sum.second;
+        list += (double)sum.first;
+      }
+    N.rest_pot = near_form(pl, (int)(points / count[kNearWave]), list / count[kNearWave],
+                           (int64_t)cut.size(), false);
+  }
+  N.n_wide256 = count[kNearWide256];
   N.n_wide = count[kNearWide];
   N.n_wide64 = count[kNearWide64];
   Upload up;

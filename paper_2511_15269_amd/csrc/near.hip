@@ -193,8 +193,9 @@ __global__ __launch_bounds__(64) void k_p2p(
 // nt mod 64 lanes of every wave in k_p2p; a record read from LDS (32 bytes a
 // lane, the same for a group) serves two pairs, since one pair per read keeps
 // the LDS as busy as the VALU.  Bound by VALU issue.  Measured (near field,
-// FP32): 200003 Plummer points, 49 a leaf, 3.42 -> 3.12 ms; 16 problems of 16
-// to 122 points a leaf 1.61 -> 1.37 ms.
+// FP32): 200003 Plummer points, 49 a leaf, 3.42 -> 3.00 ms; 16 problems of 22
+// to 109 points a leaf 1.61 -> 1.36 ms; 30011 points on a sphere, 779 items,
+// 75 -> 33 us with 256 threads an item.
 template <bool FIELD, int W>
 __global__ __launch_bounds__(W) __attribute__((amdgpu_waves_per_eu(4))) void k_p2p_wide(
     int64_t n, int item0, const int32_t* __restrict__ item_leaf,
@@ -212,7 +213,7 @@ __global__ __launch_bounds__(W) __attribute__((amdgpu_waves_per_eu(4))) void k_p
   __shared__ __align__(32) double2 stage[2 * kWideStage];
   __shared__ T sums[2 * NC][W];
   __shared__ int ljs[W], lcnt[W];  // source leaves: first point, count
-  __shared__ int lmax[2], lself[2];
+  __shared__ int lmax[W / 64], lself[W / 64];
   const int item = item0 + (int)xcd_chunked<64>(blockIdx.x, gridDim.x);
   const int tid = threadIdx.x;
   const int leaf = item_leaf[item];
@@ -259,8 +260,14 @@ __global__ __launch_bounds__(W) __attribute__((amdgpu_waves_per_eu(4))) void k_p
         lself[tid / 64] = self;
       }
       __syncthreads();
-      const int most = __builtin_amdgcn_readfirstlane(max(lmax[0], lmax[W / 64 - 1]));
-      const int self = __builtin_amdgcn_readfirstlane(max(lself[0], lself[W / 64 - 1]));
+      int most = lmax[0], self = lself[0];
+#pragma unroll
+      for (int v = 1; v < W / 64; ++v) {
+        most = max(most, lmax[v]);
+        self = max(self, lself[v]);
+      }
+      most = __builtin_amdgcn_readfirstlane(most);
+      self = __builtin_amdgcn_readfirstlane(self);
       for (int k0 = 0; k0 < nk; k0 += ng) {
         const int kn = min(ng, nk - k0);
         const bool mine = g < kn;
@@ -556,15 +563,24 @@ void run_near(fmm_plan* pl, const ListSet& Ls, const Src<T>* src, int64_t n, T* 
   // the wide forms take the leaves they were given (near_form) unless another
   // number of source groups than the plan's own is asked for
   const bool own = G == default_p2p_groups(pl);
-  const int64_t w0 = own ? N.n_wide : 0, w1 = own ? N.n_wide64 : 0, rest = w0 + w1;
+  const int64_t w2 = own ? N.n_wide256 : 0, w0 = own ? N.n_wide : 0, w1 = own ? N.n_wide64 : 0,
+                rest = w2 + w0 + w1;
   auto all = [&](auto field_tag) {
     constexpr bool F = decltype(field_tag)::value;
     if constexpr (sizeof(T) == 8) {
       launch(k_p2p_flat<F, 128>, 128, 0, w0);
       launch(k_p2p_flat<F, 64>, 64, w0, w1);
     } else {
-      launch(k_p2p_wide<F, 128>, 128, 0, w0);
-      launch(k_p2p_wide<F, 64>, 64, w0, w1);
+      launch(k_p2p_wide<F, 256>, 256, 0, w2);
+      launch(k_p2p_wide<F, 128>, 128, w2, w0);
+      launch(k_p2p_wide<F, 64>, 64, w2 + w0, w1);
+    }
+    if constexpr (sizeof(T) == 4 && !F) {
+      if (own && N.rest_pot != kNearWave) {
+        if (N.rest_pot == kNearWide64) launch(k_p2p_wide<F, 64>, 64, rest, N.n - rest);
+        else launch(k_p2p_wide<F, 128>, 128, rest, N.n - rest);
+        return;
+      }
     }
     if (G == 1) launch(k_p2p<T, F, 1>, 64, rest, N.n - rest);
     else if (G == 2) launch(k_p2p<T, F, 2>, 64, rest, N.n - rest);

@@ -20,25 +20,40 @@ int p2p_groups(const fmm_plan* pl) {
   if (pl->p2p_groups && valid_p2p_groups(pl, pl->p2p_groups)) return pl->p2p_groups;
   return default_p2p_groups(pl);
 }
-int near_form(const fmm_plan* pl, int nt, int64_t list, int64_t items) {
-  const bool fp64 = pl->prm.precision == FMM_FP64;
-  if (!fp64 && default_p2p_groups(pl) > 1) return kNearWave;
+int near_form(const fmm_plan* pl, int nt, double list, int64_t items, bool field) {
   const int h = (nt + 1) / 2;
-  const double wave = fp64 && default_p2p_groups(pl) > 1 ? 0.0 : nt / (64.0 * ((nt + 63) / 64));
-  const double len = (double)list / (double)items;  // source leaves of an item
+  if (pl->prm.precision == FMM_FP64) {
+    int form = kNearWave;
+    double best = default_p2p_groups(pl) > 1 ? 0.0 : nt / (64.0 * ((nt + 63) / 64));
+    for (int W : {64, 128}) {
+      if (nt > 2 * W) continue;  // two targets a thread
+      // the groups share out the points; the larger block has to be worth
+      // its barriers and its set-up
+      const double rate = kFlatRate * nt * (W / h) / (2.0 * W);
+      if (rate > (form == kNearWide64 ? kFlatGain * best : best)) {
+        best = rate;
+        form = W == 128 ? kNearWide : kNearWide64;
+      }
+    }
+    return form;
+  }
+  if (default_p2p_groups(pl) > 1) return kNearWave;
+  const WideRates& R = field ? kWideField : kWidePot;
+  const double per_simd = items / 1024.0;
   int form = kNearWave;
-  double best = wave;
-  for (int W : {64, 128}) {
-    // targets at a time: two a thread, in FP32 no fewer than two groups
-    if (nt > (fp64 ? 2 * W : W)) continue;
+  double best = nt / (64.0 * ((nt + 63) / 64)) * per_simd / (per_simd + 1.0);
+  for (int W : {64, 128, 256}) {
+    // two groups of two targets a thread, or more; 256 threads only for fill
+    if (nt > W || (W == 256 && per_simd >= kWideFillWaves)) continue;
     const int ng = W / h;
-    // share of busy lanes; in FP32 the list's leaves go to the groups in rounds
-    const double rounds = fp64 ? len / ng : std::ceil(len / ng);
-    const double rate = kWideRate * nt * len / (2.0 * W * rounds);
-    // the larger block has to be worth its barriers and its set-up
-    if (rate > (form == kNearWide64 ? kWideGain * best : best)) {
-      best = rate;
-      form = W == 128 ? kNearWide : kNearWide64;
+    const double full = std::floor(list / ng), rem = list - full * ng;
+    const double waves = full * std::ceil(ng * h / 64.0) + std::ceil(rem * h / 64.0);
+    const double x = per_simd * (W / 64);
+    const double rate = W == 64 ? R.w64 : (W == 128 ? R.w128 : R.w256);
+    const double r = rate * nt * list / (128.0 * waves) * x / (x + 1.0);
+    if (r > best) {
+      best = r;
+      form = W == 256 ? kNearWide256 : (W == 128 ? kNearWide : kNearWide64);
     }
   }
   return form;
