@@ -7,7 +7,8 @@
 // every slices-th run of 64 sources, so that a few targets still fill the
 // chip (one lane per target left 224 of the 256 CUs idle for 8192 targets).
 // Bound by FP64 VALU issue.  Measured: 8192 targets of 2^20 charges, FP64
-// potential and field, 99.5 -> 9.1 ms.
+// potential and field, 99.3 -> 7.8 ms (9.0 ms with two Newton steps a root and
+// every run of 64 sources checked against n).
 // Pairs at distance 0 contribute nothing.
 #include "internal.h"
 
@@ -17,11 +18,13 @@ namespace {
 constexpr double kInv4Pi = 0.079577471545947667884441881686257181;
 constexpr int kWaves = 16;
 
+// 1 / sqrt(r2): the hardware's estimate y with e = 1 - r2 y^2 (2^-24 or so)
+// and the series of (1 - e)^(-1/2) up to e^2; five operations, the remainder
+// (5/16) e^3 is far below a rounding.
 __device__ __forceinline__ double rsq(double r2) {
-  double y = __builtin_amdgcn_rsq(r2);
-  y = y * (1.5 - 0.5 * r2 * y * y);
-  y = y * (1.5 - 0.5 * r2 * y * y);
-  return y;
+  const double y = __builtin_amdgcn_rsq(r2);
+  const double e = fma(-(r2 * y), y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 __device__ __forceinline__ float rsq(float r2) { return __builtin_amdgcn_rsqf(r2); }
 
@@ -55,12 +58,9 @@ __global__ __launch_bounds__(64 * kWaves) void k_direct(
     for (int c = 0; c < NC; ++c) s[r][c] = T(0);
   if (t0 < nt) {
     const int64_t step = (int64_t)slices * 64;
-    for (int64_t j0 = (int64_t)slice * 64; j0 < n; j0 += step) {
-      const int64_t j = j0 + lane;
-      const bool live = j < n;
-      const int64_t jj = live ? j : 0;
-      const double sx = pos[3 * jj], sy = pos[3 * jj + 1], sz = pos[3 * jj + 2];
-      const T qj = q[jj];
+    auto run = [&](int64_t j, bool live) {
+      const double sx = pos[3 * j], sy = pos[3 * j + 1], sz = pos[3 * j + 2];
+      const T qj = q[j];
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         const T dx = T(x[r] - sx), dy = T(y[r] - sy), dz = T(z[r] - sz);
@@ -75,7 +75,10 @@ __global__ __launch_bounds__(64 * kWaves) void k_direct(
           s[r][3] = fma(q3, dz, s[r][3]);
         }
       }
-    }
+    };
+    int64_t j0 = (int64_t)slice * 64;
+    for (; j0 + 64 <= n; j0 += step) run(j0 + lane, true);
+    if (j0 < n) run(j0 + lane < n ? j0 + lane : 0, j0 + lane < n);
   }
 #pragma unroll
   for (int r = 0; r < R; ++r)
@@ -104,9 +107,11 @@ __global__ __launch_bounds__(64 * kWaves) void k_direct(
   }
 }
 
-// Targets per wave: as many as leave at least kFill blocks (one target group
-// per wave, or all waves on one group); slices: as few waves per group as
-// leave kFill blocks.
+// Targets per wave: as few as go into one round of kFill blocks (a block fills
+// a CU), 4 at most, since a round of 2 takes 1.3 times and of 4 twice as long
+// as a round of 1 (2^20 charges, FP64 potential and field: 64 targets 0.48, 512
+// 0.64, 1024 1.00 ms; 300 targets with one a wave, two rounds, 0.97 ms);
+// slices: as few waves per group as leave kFill blocks.
 constexpr int64_t kFill = 256;
 
 template <typename T, int R>
@@ -128,9 +133,9 @@ void launch(int64_t n, const double* pos, const void* q, const int64_t* targets,
 template <typename T>
 void choose(int64_t n, const double* pos, const void* q, const int64_t* targets, int64_t nt,
             void* pot, void* field, hipStream_t st) {
-  if (nt >= 4 * kFill)
+  if (nt > 2 * kFill)
     launch<T, 4>(n, pos, q, targets, nt, pot, field, st);
-  else if (nt >= 2 * kFill)
+  else if (nt > kFill)
     launch<T, 2>(n, pos, q, targets, nt, pot, field, st);
   else
     launch<T, 1>(n, pos, q, targets, nt, pot, field, st);
