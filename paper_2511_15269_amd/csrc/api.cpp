@@ -401,8 +401,15 @@ void check_device(const fmm_plan* pl) {
 }
 
 // Several charge vectors: FP32 plans built for more than one vector take
-// them kRB at a time through the multi-vector kernels; otherwise one pass
-// per vector.
+// them kRB at a time through the multi-vector kernels; otherwise, and for the
+// few vectors that are quicker so, one pass per vector.  The multi-vector
+// pass costs the same for 1 to 16 and for 17 to 32 vectors; measured, one
+// vector alone | 16 | 32 together: 4000 points 71 | 243 | 296 us, 30000 131 |
+// 715 | 1007 (p = 6) and 135 | 1377 | 1397 (p = 8), 130000 111 | 590 | 726
+// (p = 4) to 226 | 3497 | 3681 (p = 10), 2^18 300 | 2059 | 2536.
+constexpr int kFewVectors = 5, kFewVectorsSmall = 3;
+constexpr int64_t kFewVectorsPoints = 1 << 14;
+
 void run_vectors(fmm_plan* pl, int dir, const void* q, int nrhs, void* pot, void* field,
                  hipStream_t st) {
   if (nrhs > 1 && pl->ws.bq) {
@@ -410,8 +417,13 @@ void run_vectors(fmm_plan* pl, int dir, const void* q, int nrhs, void* pot, void
     const int64_t n = pl->n;
     for (int r0 = 0; r0 < nrhs; r0 += W) {
       const int R = std::min(W, nrhs - r0);
-      evaluate_batch(pl, dir, (const float*)q + (int64_t)r0 * n, R, (float*)pot + (int64_t)r0 * n,
-                     field ? (float*)field + 3 * (int64_t)r0 * n : nullptr, st);
+      const float* qr = (const float*)q + (int64_t)r0 * n;
+      float* ur = (float*)pot + (int64_t)r0 * n;
+      float* fr = field ? (float*)field + 3 * (int64_t)r0 * n : nullptr;
+      if (R <= (n < kFewVectorsPoints ? kFewVectorsSmall : kFewVectors))
+        evaluate(pl, pl->ws, dir, qr, R, ur, fr, st);
+      else
+        evaluate_batch(pl, dir, qr, R, ur, fr, st);
     }
   } else {
     evaluate(pl, pl->ws, dir, q, nrhs, pot, field, st);

@@ -339,7 +339,7 @@ void run_batch(fmm_plan* pl, const ListSet& Ls, const float* q, int R, float* po
                                                 tab, potL, fldL);
   mk.end(kStL2P, st);
   mk.begin(kStP2P, st);
-  batch_near(pl, Ls, qL, potL, fldL, st);
+  batch_near(pl, Ls, R, qL, potL, fldL, st);
   batch_scatter(pl, R, potL, fldL, pot, field, st);
   mk.end(kStP2P, st);
   FMM_HIP(hipGetLastError());

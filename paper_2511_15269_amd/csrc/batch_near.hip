@@ -7,7 +7,7 @@
 //         vectors the B operand of v_mfma_f32_16x16x4f32; accumulators hold
 //         the potential and the three field components for 16 targets x 32
 //         vectors.  Each source leaf is accumulated from zero and added to
-//         the running sums with Neumaier compensation.
+//         running sums in FP64.
 #include <type_traits>
 
 #include "internal.h"
@@ -23,15 +23,10 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 inline unsigned blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
-// Neumaier's compensated addition, elementwise: s + c carries the sum.
-__device__ __forceinline__ void neumaier4(floatx4& s, floatx4& c, floatx4 x) {
-  const floatx4 t = s + x;
+// s += x, elementwise, s in FP64
+__device__ __forceinline__ void add4(double (&s)[4], floatx4 x) {
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const float sv = s[v], xv = x[v], tv = t[v];
-    c[v] += fabsf(sv) >= fabsf(xv) ? (sv - tv) + xv : (xv - tv) + sv;
-  }
-  s = t;
+  for (int v = 0; v < 4; ++v) s[v] += double(x[v]);
 }
 
 // The sort stage: the caller's charges (vector-major [R][n], input order)
@@ -67,18 +62,25 @@ __global__ __launch_bounds__(256) void k_bgather(int64_t n, int R,
 // column l % 16 (+16 in the second half).  Source points (positions and the
 // 32 charges) are staged in LDS, up to kStage points at a time, with
 // coalesced loads.  A block holds TW waves, one 16-target tile each, that
-// share every staged chunk.  Small tiles keep the accumulators to 32
+// share every staged chunk.  H: column halves, 1 for up to 16 vectors.  Small tiles keep the accumulators to 32
 // registers per lane; the kernel is held to three waves per SIMD (146
 // registers, no spills), so that the kernel values of one wave's next step
-// are computed while another wave's MFMAs run.
+// are computed while another wave's MFMAs run.  Bound by issue: the MFMAs take
+// 58% of the SIMDs' cycles and the vector instructions, which do not overlap
+// them, the rest.  So the leaf sums go to FP64 running sums (two instructions
+// an element; compensated FP32 sums took eight, 16 of the 39 vector
+// instructions a step) and distance 0 is looked for only in the target leaf
+// itself, or everywhere when points coincide.  Measured (2^18 points, 64 a
+// leaf, theta = 0.8): 32 vectors 1.37 -> 1.26 ms.
 constexpr int kStage = 64;
 
-template <int TW>
+template <int TW, int H>
 __global__ __launch_bounds__(64 * TW) __attribute__((amdgpu_waves_per_eu(3))) void k_bp2p(
     const int32_t* __restrict__ leaf_start, const double* __restrict__ xs,
     const double* __restrict__ ys, const double* __restrict__ zs,
     const float* __restrict__ qL, const int32_t* __restrict__ p2p_ptr,
-    const int32_t* __restrict__ p2p_src, float* __restrict__ potL, float* __restrict__ fldL) {
+    const int32_t* __restrict__ p2p_src, int dup, float* __restrict__ potL,
+    float* __restrict__ fldL) {
   __shared__ double px[kStage], py[kStage], pz[kStage];
   // charge rows padded to 48 floats: the four source rows a step reads sit
   // 16 banks apart, so a half-wave's 32 lanes hit 32 distinct banks
@@ -95,17 +97,16 @@ __global__ __launch_bounds__(64 * TW) __attribute__((amdgpu_waves_per_eu(3))) vo
   for (int tl = 0; tl < ntile; ++tl) {
     const int i0 = st + 16 * (tl * TW + wv);
     const int i = i0 + row;
-    const bool live_i = i < en;
-    const int ii = live_i ? i : st;
+    const int ii = i < en ? i : st;  // rows past the leaf's end are not stored
     const double xi = xs[ii], yi = ys[ii], zi = zs[ii];
-    // running sums (s*) with Neumaier compensation (c*) for the two column
-    // halves (0, 1); each source leaf is accumulated on the matrix cores
-    // from zero and then added
-    floatx4 su0 = {}, sx0 = {}, sy0 = {}, sz0 = {}, su1 = {}, sx1 = {}, sy1 = {}, sz1 = {};
-    floatx4 cu0 = {}, cx0 = {}, cy0 = {}, cz0 = {}, cu1 = {}, cx1 = {}, cy1 = {}, cz1 = {};
+    // running sums for the two column halves (0, 1); each source leaf is
+    // accumulated on the matrix cores from zero and then added
+    double su0[4] = {}, sx0[4] = {}, sy0[4] = {}, sz0[4] = {};
+    double su1[4] = {}, sx1[4] = {}, sy1[4] = {}, sz1[4] = {};
     for (int k = pb; k < pe; ++k) {
       const int sl = p2p_src[k];
       const int js = leaf_start[sl], je = leaf_start[sl + 1];
+      const bool safe = dup || sl == leaf;
       floatx4 au0 = {}, ax0 = {}, ay0 = {}, az0 = {}, au1 = {}, ax1 = {}, ay1 = {}, az1 = {};
       for (int c0 = js; c0 < je; c0 += kStage) {
         const int cnt = min(kStage, je - c0);
@@ -122,61 +123,68 @@ __global__ __launch_bounds__(64 * TW) __attribute__((amdgpu_waves_per_eu(3))) vo
         }
         __syncthreads();
         // one step: four source points j0 .. j0+3 (lane group kk takes j0+kk)
-        auto step = [&](int j0, auto check_tag) {
+        // CHECK: some of them may be past the chunk; SAFE: pairs at distance 0
+        // contribute nothing (otherwise the pairs are known to be apart)
+        auto step = [&](int j0, auto check_tag, auto safe_tag) {
           constexpr bool CHECK = decltype(check_tag)::value;
+          constexpr bool SAFE = decltype(safe_tag)::value;
           const int j = j0 + kk;
           const bool live_j = !CHECK || j < cnt;
           const int jj = CHECK ? (live_j ? j : 0) : j;
           const float dx = float(xi - px[jj]), dy = float(yi - py[jj]), dz = float(zi - pz[jj]);
           const float r2 = dx * dx + dy * dy + dz * dz;
           const float inv0 = __builtin_amdgcn_rsqf(r2);
-          const float inv = (r2 > 0.f && live_i && live_j) ? inv0 : 0.f;
+          const float inv = !SAFE || (r2 > 0.f && live_j) ? inv0 : 0.f;
           const float inv3 = inv * inv * inv;
-          const float q0 = qs[jj][row], q1 = qs[jj][16 + row];
+          const float q0 = qs[jj][row], q1 = H == 2 ? qs[jj][16 + row] : 0.f;
           const float b0 = live_j ? q0 : 0.f;
           const float b1 = live_j ? q1 : 0.f;
           const float ex = dx * inv3, ey = dy * inv3, ez = dz * inv3;
           au0 = __builtin_amdgcn_mfma_f32_16x16x4f32(inv, b0, au0, 0, 0, 0);
-          au1 = __builtin_amdgcn_mfma_f32_16x16x4f32(inv, b1, au1, 0, 0, 0);
+          if (H == 2) au1 = __builtin_amdgcn_mfma_f32_16x16x4f32(inv, b1, au1, 0, 0, 0);
           ax0 = __builtin_amdgcn_mfma_f32_16x16x4f32(ex, b0, ax0, 0, 0, 0);
-          ax1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ex, b1, ax1, 0, 0, 0);
+          if (H == 2) ax1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ex, b1, ax1, 0, 0, 0);
           ay0 = __builtin_amdgcn_mfma_f32_16x16x4f32(ey, b0, ay0, 0, 0, 0);
-          ay1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ey, b1, ay1, 0, 0, 0);
+          if (H == 2) ay1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ey, b1, ay1, 0, 0, 0);
           az0 = __builtin_amdgcn_mfma_f32_16x16x4f32(ez, b0, az0, 0, 0, 0);
-          az1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ez, b1, az1, 0, 0, 0);
+          if (H == 2) az1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ez, b1, az1, 0, 0, 0);
         };
         int j0 = 0;
-        for (; j0 + 16 <= cnt; j0 += 16) {
+        auto full = [&](auto safe_tag) {
+          for (; j0 + 16 <= cnt; j0 += 16) {
 #pragma unroll
-          for (int u = 0; u < 4; ++u) step(j0 + 4 * u, std::false_type{});
-        }
-        for (; j0 < cnt; j0 += 4) step(j0, std::true_type{});
+            for (int u = 0; u < 4; ++u) step(j0 + 4 * u, std::false_type{}, safe_tag);
+          }
+        };
+        if (safe)
+          full(std::true_type{});
+        else
+          full(std::false_type{});
+        for (; j0 < cnt; j0 += 4) step(j0, std::true_type{}, std::true_type{});
       }
-      neumaier4(su0, cu0, au0);
-      neumaier4(sx0, cx0, ax0);
-      neumaier4(sy0, cy0, ay0);
-      neumaier4(sz0, cz0, az0);
-      neumaier4(su1, cu1, au1);
-      neumaier4(sx1, cx1, ax1);
-      neumaier4(sy1, cy1, ay1);
-      neumaier4(sz1, cz1, az1);
+      add4(su0, au0);
+      add4(sx0, ax0);
+      add4(sy0, ay0);
+      add4(sz0, az0);
+      if (H == 2) add4(su1, au1);
+      if (H == 2) add4(sx1, ax1);
+      if (H == 2) add4(sy1, ay1);
+      if (H == 2) add4(sz1, az1);
     }
-    const floatx4 U[2] = {su0 + cu0, su1 + cu1}, X[2] = {sx0 + cx0, sx1 + cx1},
-                  Y[2] = {sy0 + cy0, sy1 + cy1}, Z[2] = {sz0 + cz0, sz1 + cz1};
     const float c = float(kInv4Pi);
 #pragma unroll
-    for (int hf = 0; hf < 2; ++hf) {
+    for (int hf = 0; hf < H; ++hf) {
       const int col = 16 * hf + row;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int ti = i0 + 4 * kk + v;
         if (ti < en) {
           const int64_t o = ti;
-          potL[o * kRB + col] += -c * U[hf][v];
+          potL[o * kRB + col] -= c * float(hf ? su1[v] : su0[v]);
           // field = -grad u; grad of the near part is +(1/4pi) sum q d/r^3
-          fldL[(o * 3 + 0) * kRB + col] -= c * X[hf][v];
-          fldL[(o * 3 + 1) * kRB + col] -= c * Y[hf][v];
-          fldL[(o * 3 + 2) * kRB + col] -= c * Z[hf][v];
+          fldL[(o * 3 + 0) * kRB + col] -= c * float(hf ? sx1[v] : sx0[v]);
+          fldL[(o * 3 + 1) * kRB + col] -= c * float(hf ? sy1[v] : sy0[v]);
+          fldL[(o * 3 + 2) * kRB + col] -= c * float(hf ? sz1[v] : sz0[v]);
         }
       }
     }
@@ -246,17 +254,23 @@ void batch_gather(const fmm_plan* pl, const float* q, int R, float* qL, hipStrea
   k_bgather<<<blocks(pl->n, 64), 256, 0, st>>>(pl->n, R, pl->iperm, q, qL);
 }
 
-void batch_near(const fmm_plan* pl, const ListSet& Ls, const float* qL, float* potL, float* fldL,
-                hipStream_t st) {
+void batch_near(const fmm_plan* pl, const ListSet& Ls, int R, const float* qL, float* potL,
+                float* fldL, hipStream_t st) {
   const int TW = batch_p2p_waves(pl);
   auto p2p = [&](auto kern, int tw) {
     kern<<<(unsigned)pl->nleaf, 64 * tw, 0, st>>>(pl->leaf_start, pl->xs, pl->ys, pl->zs, qL,
-                                                   Ls.p2p_ptr, Ls.p2p_src, potL, fldL);
+                                                   Ls.p2p_ptr, Ls.p2p_src, pl->has_dup ? 1 : 0, potL,
+                                                   fldL);
   };
-  if (TW == 1) p2p(k_bp2p<1>, 1);
-  else if (TW == 2) p2p(k_bp2p<2>, 2);
-  else if (TW == 4) p2p(k_bp2p<4>, 4);
-  else p2p(k_bp2p<8>, 8);
+  auto all = [&](auto halves) {
+    constexpr int H = decltype(halves)::value;
+    if (TW == 1) p2p(k_bp2p<1, H>, 1);
+    else if (TW == 2) p2p(k_bp2p<2, H>, 2);
+    else if (TW == 4) p2p(k_bp2p<4, H>, 4);
+    else p2p(k_bp2p<8, H>, 8);
+  };
+  if (R <= kRB / 2) all(std::integral_constant<int, 1>{});
+  else all(std::integral_constant<int, 2>{});
 }
 
 void batch_scatter(const fmm_plan* pl, int R, const float* potL, const float* fldL, float* pot,

@@ -405,8 +405,8 @@ void evaluate(fmm_plan* pl, const Workspace& ws, int dir, const void* q, int nrh
 constexpr int kBatchWidth = 32;
 int batch_width();
 void batch_gather(const fmm_plan* pl, const float* q, int R, float* qL, hipStream_t st);
-void batch_near(const fmm_plan* pl, const ListSet& Ls, const float* qL, float* potL, float* fldL,
-                hipStream_t st);
+void batch_near(const fmm_plan* pl, const ListSet& Ls, int R, const float* qL, float* potL,
+                float* fldL, hipStream_t st);
 void batch_scatter(const fmm_plan* pl, int R, const float* potL, const float* fldL, float* pot,
                    float* field, hipStream_t st);
 template <int P>

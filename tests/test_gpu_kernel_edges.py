@@ -112,6 +112,30 @@ def test_m2l_of_every_order(fmm, prec, tol, p):
     assert _rel(f.double().cpu().numpy(), f0) <= tol
 
 
+# vectors taken one by one, in one or two column halves, and in a second pass
+# (coincident points: distance 0 is looked for everywhere)
+@pytest.mark.parametrize("n,leaf", [(2600, 47), (17000, 64)])
+@pytest.mark.parametrize("R", [4, 5, 6, 7, 16, 17, 37])
+def test_vector_counts(fmm, n, leaf, R):
+    from oracle.fmm import fmm as oracle_fmm
+    _say(f"[vectors] n={n} R={R}")
+    pos, _ = workloads.uniform_cube(n, 36)
+    if n == 2600:
+        pos[n // 2] = pos[1]
+    Q = np.random.default_rng(37).uniform(-1, 1, (R, n))
+    pt, Qt = torch.from_numpy(pos).cuda(), torch.from_numpy(Q).cuda().float()
+    kw = dict(p=5, leaf_max=leaf, splits=2, theta=0.6, precision="fp32")
+    U, Fd = fmm.Plan(pt, max_rhs=R, **kw).evaluate(Qt)
+    single = fmm.Plan(pt, **kw)
+    for r in range(R):
+        u1, f1 = single.evaluate(Qt[r])
+        assert _rel(U[r].double().cpu().numpy(), u1.double().cpu().numpy()) <= 1e-6
+        assert _rel(Fd[r].double().cpu().numpy(), f1.double().cpu().numpy()) <= 1e-6
+    u0, f0 = oracle_fmm(pos, Q[R - 1], 5, leaf, 2, 0.6)
+    assert _rel(U[R - 1].double().cpu().numpy(), u0) <= 1e-5
+    assert _rel(Fd[R - 1].double().cpu().numpy(), f0) <= 1e-5
+
+
 def test_plans_made_and_dropped_share_no_state(fmm):
     """Plans of several sizes made, evaluated and dropped in turn, from two
     threads on their own streams and around a captured graph, give each time
