@@ -405,8 +405,8 @@ void check_device(const fmm_plan* pl) {
 // few vectors that are quicker so, one pass per vector.  The multi-vector
 // pass costs the same for 1 to 16 and for 17 to 32 vectors; measured, one
 // vector alone | 16 | 32 together: 4000 points 71 | 243 | 296 us, 30000 131 |
-// 715 | 1007 (p = 6) and 135 | 1377 | 1397 (p = 8), 130000 111 | 590 | 726
-// (p = 4) to 226 | 3497 | 3681 (p = 10), 2^18 300 | 2059 | 2536.
+// 715 | 1007 (p = 6) and 135 | 970 | 1400 (p = 8), 130000 111 | 523 | 726
+// (p = 4) to 226 | 2400 | 3681 (p = 10), 2^18 300 | 1732 | 2536.
 constexpr int kFewVectors = 5, kFewVectorsSmall = 3;
 constexpr int64_t kFewVectorsPoints = 1 << 14;
 
