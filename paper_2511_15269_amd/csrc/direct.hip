@@ -60,7 +60,9 @@ __global__ __launch_bounds__(64 * kWaves) void k_direct(
     const int64_t step = (int64_t)slices * 64;
     auto run = [&](int64_t j, bool live) {
       const double sx = pos[3 * j], sy = pos[3 * j + 1], sz = pos[3 * j + 2];
-      const T qj = q[j];
+      // a lane past n reads point 0, whose charge must not count even times 0
+      // (it may be infinite)
+      const T qj = live ? q[j] : T(0);
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         const T dx = T(x[r] - sx), dy = T(y[r] - sy), dz = T(z[r] - sz);
