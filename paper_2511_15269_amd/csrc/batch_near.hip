@@ -70,7 +70,7 @@ __global__ __launch_bounds__(256) void k_bgather(int64_t n, int R,
 // them, the rest.  So the leaf sums go to FP64 running sums (two instructions
 // an element; compensated FP32 sums took eight, 16 of the 39 vector
 // instructions a step) and distance 0 is looked for only in the target leaf
-// itself, or everywhere when points coincide.  Measured (2^18 points, 64 a
+// itself, or everywhere when some points cannot be told apart.  Measured (2^18 points, 64 a
 // leaf, theta = 0.8): 32 vectors 1.37 -> 1.26 ms.
 constexpr int kStage = 64;
 

@@ -222,7 +222,9 @@ struct fmm_plan {
   double* scale = nullptr;   // [nbox] length scale of the box's expansions
   fmm::BoxGeo* geo = nullptr;  // [nbox] cx, cy, cz, scale
   int32_t max_leaf_count = 0;
-  bool has_dup = true;  // some two points coincide (set by the tree build)
+  // some two points coincide or cannot be told apart in the plan's precision
+  // (set by the tree build)
+  bool has_dup = true;
   // launch tiles (0: the default rule from max_leaf_count; set by
   // fmm_plan_autotune): P2P source groups, P2M/L2P leaves per wave
   int p2p_groups = 0;

@@ -16,7 +16,8 @@ using namespace ops;
 // gives 2 / r, one operation less than 1 / r (near_scale takes the powers of
 // two out again: 17 instead of 18 operations).  SAFE: pairs at distance 0
 // contribute nothing (needed within a leaf, and between leaves when the
-// point set has coincident points); otherwise the pair is known to be apart.
+// point set has points at a distance that is 0 in T); otherwise the pair is
+// known to be apart.
 template <typename T, bool FIELD, bool SAFE>
 __device__ __forceinline__ void p2p_pair(const Src<T>& s, double xi, double yi, double zi,
                                          T& u, T& gx, T& gy, T& gz) {
@@ -96,7 +97,7 @@ __global__ __launch_bounds__(64) void k_p2p(
       T lu = T(0), lx = T(0), ly = T(0), lz = T(0);
       const int full = cnt / G;  // points per group present in every group
       // distance-0 guard only where it can matter: the target leaf itself,
-      // or every leaf when the point set has coincident points
+      // or every leaf when some points of the set cannot be told apart
       const bool safe = dup || sl == leaf;
       const Src<T>* rec;
       int stride;

@@ -154,37 +154,112 @@ __global__ void k_gather_pos(int n, const int32_t* __restrict__ perm,
 
 inline unsigned blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
-// Hash of a position (equal positions give equal hashes; -0 and +0 alike).
+// Points that the near field cannot tell apart: the squared distance, formed as
+// the pairs of the near field form it, is 0 in the plan's precision T.  That
+// takes coordinates that differ by 2^-75 (FP32) or 2^-537 (FP64) at the most,
+// equal ones or some within about 1e-7 (FP32) of 0.  They are looked for among
+// the points of one cell of a grid of spacing 1 / kCells; a pair can also lie
+// on both sides of a cell's face, then both points are within kEdge cells of it.
+template <typename T>
+struct CloseGrid;
+template <>
+struct CloseGrid<float> {
+  static constexpr double kCells = 0x1p50, kEdge = 0x1p-24;
+};
+template <>
+struct CloseGrid<double> {
+  static constexpr double kCells = 0x1p500, kEdge = 0x1p-36;
+};
+constexpr int kEdgePoints = 64;  // points near a face that are checked one by one
+
+template <typename T>
+__device__ bool close_pair(int a, int b, const double* __restrict__ xs,
+                           const double* __restrict__ ys, const double* __restrict__ zs) {
+  const T dx = T(xs[a] - xs[b]), dy = T(ys[a] - ys[b]), dz = T(zs[a] - zs[b]);
+  return !(dx * dx + dy * dy + dz * dz > T(0));
+}
+
+// Hash of the cell of a position (-0 and +0 alike).  found[1] counts the points
+// near a face of their cell, found[2 ...] are the first kEdgePoints of them.
+template <typename T>
 __global__ void k_pos_hash(int n, const double* __restrict__ xs, const double* __restrict__ ys,
-                           const double* __restrict__ zs, uint64_t* __restrict__ h) {
+                           const double* __restrict__ zs, uint64_t* __restrict__ h,
+                           int* __restrict__ found) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  auto bits = [](double v) { return (uint64_t)__double_as_longlong(v + 0.0); };
+  bool edge = false;
+  auto bits = [&](double v) {
+    const double s = v * CloseGrid<T>::kCells;
+    // a coordinate this far out is a multiple of the spacing itself
+    if (!(fabs(s) < 0x1p52)) return (uint64_t)__double_as_longlong(v);
+    const double r = rint(s);
+    // (from 2^30 cells on, neighbouring numbers are further apart than kEdge)
+    edge = edge || (fabs(s) < 0x1p30 && fabs(fabs(s - r) - 0.5) <= CloseGrid<T>::kEdge);
+    return (uint64_t)__double_as_longlong(r + 0.0);
+  };
   uint64_t a = bits(xs[i]) * 0x9E3779B97F4A7C15ull;
   uint64_t b = bits(ys[i]) * 0xC2B2AE3D27D4EB4Full;
   uint64_t c = bits(zs[i]) * 0x165667B19E3779F9ull;
   a ^= (b << 21) | (b >> 43);
   a ^= (c << 42) | (c >> 22);
   h[i] = a ^ (a >> 29);
+  if (edge) {
+    const int at = atomicAdd(&found[1], 1);
+    if (at < kEdgePoints) found[2 + at] = i;
+  }
 }
 
-// After sorting by hash: flag a pair of coincident points.  Within a run of
-// equal hashes every element is compared with up to kWalk predecessors; a
-// longer run counts as coincident (conservative).
-__global__ void k_dup_check(int n, const uint64_t* __restrict__ h, const int32_t* __restrict__ idx,
-                            const double* __restrict__ xs, const double* __restrict__ ys,
-                            const double* __restrict__ zs, int* __restrict__ flag) {
+// After sorting by hash: sets found[0] if there is a pair that cannot be told
+// apart.  Within a run of equal hashes every element is compared with up to
+// kWalk predecessors; a longer run counts as such a pair (conservative).
+template <typename T>
+__global__ void k_close_check(int n, const uint64_t* __restrict__ h,
+                              const int32_t* __restrict__ idx, const double* __restrict__ xs,
+                              const double* __restrict__ ys, const double* __restrict__ zs,
+                              int* __restrict__ found) {
   constexpr int kWalk = 32;
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < 1 || i >= n || h[i] != h[i - 1]) return;
   const int a = idx[i];
   for (int j = i - 1, w = 0; j >= 0 && h[j] == h[i]; --j, ++w) {
-    const int b = idx[j];
-    if (w == kWalk || (xs[a] == xs[b] && ys[a] == ys[b] && zs[a] == zs[b])) {
-      *flag = 1;
+    if (w == kWalk || close_pair<T>(a, idx[j], xs, ys, zs)) {
+      found[0] = 1;
       return;
     }
   }
+}
+
+// The listed points near a face (blockIdx.y) against all points.
+template <typename T>
+__global__ void k_edge_check(int n, const double* __restrict__ xs, const double* __restrict__ ys,
+                             const double* __restrict__ zs, int* __restrict__ found) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  const int a = found[2 + blockIdx.y];
+  if (i < n && i != a && close_pair<T>(a, i, xs, ys, zs)) found[0] = 1;
+}
+
+// Whether some two points of the leaf-ordered coordinates of pl cannot be told
+// apart (P2P then guards every pair, not only the pairs inside one leaf).  keys,
+// keys_out, idx, temp: scratch of the sort; found: 2 + kEdgePoints ints.
+template <typename T>
+bool any_close(fmm_plan* pl, uint64_t* keys, uint64_t* keys_out, const int32_t* iota, int32_t* idx,
+               void* temp, size_t temp_bytes, int* found, hipStream_t st) {
+  const int n = (int)pl->n, B = 256;
+  int host[2] = {0, 0};
+  FMM_HIP(hipMemsetAsync(found, 0, sizeof(host), st));
+  k_pos_hash<T><<<blocks(n, B), B, 0, st>>>(n, pl->xs, pl->ys, pl->zs, keys, found);
+  sort_pairs_u64_i32(temp, temp_bytes, keys, keys_out, iota, idx, n, st);
+  k_close_check<T><<<blocks(n, B), B, 0, st>>>(n, keys_out, idx, pl->xs, pl->ys, pl->zs, found);
+  FMM_HIP(hipGetLastError());
+  FMM_HIP(hipMemcpyAsync(host, found, sizeof(host), hipMemcpyDeviceToHost, st));
+  FMM_HIP(hipStreamSynchronize(st));
+  if (host[0] || host[1] > kEdgePoints) return true;
+  if (host[1] == 0) return false;
+  k_edge_check<T><<<dim3(blocks(n, B), host[1]), B, 0, st>>>(n, pl->xs, pl->ys, pl->zs, found);
+  FMM_HIP(hipGetLastError());
+  FMM_HIP(hipMemcpyAsync(host, found, sizeof(int), hipMemcpyDeviceToHost, st));
+  FMM_HIP(hipStreamSynchronize(st));
+  return host[0] != 0;
 }
 
 }  // namespace
@@ -206,7 +281,7 @@ void build_tree(fmm_plan* pl, const double* pos, hipStream_t st) {
   int32_t* base = (int32_t*)sc.get(sizeof(int32_t) * 4 * (size_t)n);
   int32_t* base2 = (int32_t*)sc.get(sizeof(int32_t) * 4 * (size_t)n);
   auto list = [&](int a) { return base + (size_t)a * n; };
-  int* bad = (int*)sc.get(sizeof(int));
+  int* bad = (int*)sc.get(sizeof(int) * (2 + kEdgePoints));
   FMM_HIP(hipMemsetAsync(bad, 0, sizeof(int), st));
 
   k_soa_keys<<<blocks(n, T), T, 0, st>>>(pos, n, X, keys, iota, bad);
@@ -296,16 +371,9 @@ void build_tree(fmm_plan* pl, const double* pos, hipStream_t st) {
   int mx = 0;
   for (int b = 0; b < nseg; ++b) mx = std::max(mx, seg[b + 1] - seg[b]);
   pl->max_leaf_count = mx;
-  // coincident points anywhere? (P2P then guards every pair, not only the
-  // pairs inside one leaf)
-  k_pos_hash<<<blocks(n, T), T, 0, st>>>(n, pl->xs, pl->ys, pl->zs, keys);
-  sort_pairs_u64_i32(temp, tb, keys, keys_out, iota, base2, n, st);
-  FMM_HIP(hipMemsetAsync(bad, 0, sizeof(int), st));
-  k_dup_check<<<blocks(n, T), T, 0, st>>>(n, keys_out, base2, pl->xs, pl->ys, pl->zs, bad);
-  FMM_HIP(hipGetLastError());
-  FMM_HIP(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, st));
-  FMM_HIP(hipStreamSynchronize(st));
-  pl->has_dup = hbad != 0;
+  pl->has_dup = pl->prm.precision == FMM_FP32
+                    ? any_close<float>(pl, keys, keys_out, iota, base2, temp, tb, bad, st)
+                    : any_close<double>(pl, keys, keys_out, iota, base2, temp, tb, bad, st);
 }
 
 }  // namespace fmm
