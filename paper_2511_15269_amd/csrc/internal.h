@@ -451,6 +451,11 @@ int default_p2p_groups(const fmm_plan* pl);
 // chip only: with 16 waves a SIMD and more they gain 0 to 4% by themselves
 // (9% for 132 to 140 points) but hold up the far field beside them (16
 // problems of 22 to 109 points a leaf, pass: 1.65 | 1.76 ms without and with).
+// The items that keep one wave with a field never take 256 threads without one
+// (rate 0): their lists of one to four leaves leave groups without a leaf, which
+// the product rates too high (near field, one wave | 128 in two rounds of
+// targets | 256 threads: 2^8 leaves of 200 points 148 | 178 | 162 us, of 256 187
+// | 221 | 204; 2^9 of 160 139 | 145 | 131).
 // FP64 leaves of a plan with two or four source groups (32 points and fewer)
 // always take the wide form; in FP32 the wide forms reproduce the sums of one
 // source group, so such plans keep k_p2p.
@@ -458,7 +463,7 @@ enum { kNearWide256 = 0, kNearWide = 1, kNearWide64 = 2, kNearWave = 3 };
 struct WideRates {
   double w64, w128, w256;
 };
-constexpr WideRates kWideField{1.0, 0.97, 0.88}, kWidePot{1.12, 1.05, 0.95};
+constexpr WideRates kWideField{1.0, 0.97, 0.88}, kWidePot{1.12, 1.05, 0.0};
 constexpr double kWideFillWaves = 16.0;
 // FP64: the flat form's rate, and what 128 threads have to gain on 64
 constexpr double kFlatRate = 0.9, kFlatGain = 1.08;

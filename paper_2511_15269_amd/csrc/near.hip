@@ -549,46 +549,68 @@ __global__ __launch_bounds__(64) void k_p2p_sum(
   }
 }
 
+// Items [first, first + count) of a pass on one form (near_form).
+struct NearRun {
+  int form;
+  int64_t first, count;
+};
+
+// The launches of a pass over Ls, each on the form its items were given
+// (at most four, some possibly empty); returns their number.
+int near_runs(const fmm_plan* pl, const ListSet& Ls, bool field, NearRun (&run)[4]) {
+  const NearItems& N = Ls.near;
+  int k = 0;
+  int64_t at = 0;
+  auto add = [&](int form, int64_t count) {
+    run[k++] = NearRun{form, at, count};
+    at += count;
+  };
+  // the wide forms take the leaves they were given unless another number of
+  // source groups than the plan's own is asked for
+  if (p2p_groups(pl) != default_p2p_groups(pl)) {
+    add(kNearWave, N.n);
+    return k;
+  }
+  add(kNearWide256, N.n_wide256);
+  add(kNearWide, N.n_wide);
+  add(kNearWide64, N.n_wide64);
+  add(field ? kNearWave : N.rest_pot, N.n - at);
+  return k;
+}
+
 template <typename T>
 void run_near(fmm_plan* pl, const ListSet& Ls, const Src<T>* src, int64_t n, T* near, bool field,
               hipStream_t sp) {
   const NearItems& N = Ls.near;
   const int G = p2p_groups(pl);
-  // items [first, first + count) on kern, `threads` a block
-  auto launch = [&](auto kern, int threads, int64_t first, int64_t count) {
-    if (count == 0) return;
-    kern<<<(unsigned)count, threads, 0, sp>>>(n, (int)first, N.leaf, N.kb, N.ke, N.out,
-                                              pl->leaf_start, pl->xs, pl->ys, pl->zs, src,
-                                              Ls.p2p_src, pl->has_dup ? 1 : 0, near, (T*)N.part);
-  };
-  // the wide forms take the leaves they were given (near_form) unless another
-  // number of source groups than the plan's own is asked for
-  const bool own = G == default_p2p_groups(pl);
-  const int64_t w2 = own ? N.n_wide256 : 0, w0 = own ? N.n_wide : 0, w1 = own ? N.n_wide64 : 0,
-                rest = w2 + w0 + w1;
-  auto all = [&](auto field_tag) {
+  NearRun run[4];
+  const int runs = near_runs(pl, Ls, field, run);
+  auto all = [&](const NearRun& r, auto field_tag) {
     constexpr bool F = decltype(field_tag)::value;
-    if constexpr (sizeof(T) == 8) {
-      launch(k_p2p_flat<F, 128>, 128, 0, w0);
-      launch(k_p2p_flat<F, 64>, 64, w0, w1);
+    auto launch = [&](auto kern, int threads) {
+      kern<<<(unsigned)r.count, threads, 0, sp>>>(n, (int)r.first, N.leaf, N.kb, N.ke, N.out,
+                                                  pl->leaf_start, pl->xs, pl->ys, pl->zs, src,
+                                                  Ls.p2p_src, pl->has_dup ? 1 : 0, near,
+                                                  (T*)N.part);
+    };
+    if (r.form == kNearWave) {
+      if (G == 1) launch(k_p2p<T, F, 1>, 64);
+      else if (G == 2) launch(k_p2p<T, F, 2>, 64);
+      else launch(k_p2p<T, F, 4>, 64);
+    } else if constexpr (sizeof(T) == 8) {
+      if (r.form == kNearWide) launch(k_p2p_flat<F, 128>, 128);
+      else launch(k_p2p_flat<F, 64>, 64);
     } else {
-      launch(k_p2p_wide<F, 256>, 256, 0, w2);
-      launch(k_p2p_wide<F, 128>, 128, w2, w0);
-      launch(k_p2p_wide<F, 64>, 64, w2 + w0, w1);
+      if (r.form == kNearWide256) launch(k_p2p_wide<F, 256>, 256);
+      else if (r.form == kNearWide) launch(k_p2p_wide<F, 128>, 128);
+      else launch(k_p2p_wide<F, 64>, 64);
     }
-    if constexpr (sizeof(T) == 4 && !F) {
-      if (own && N.rest_pot != kNearWave) {
-        if (N.rest_pot == kNearWide64) launch(k_p2p_wide<F, 64>, 64, rest, N.n - rest);
-        else launch(k_p2p_wide<F, 128>, 128, rest, N.n - rest);
-        return;
-      }
-    }
-    if (G == 1) launch(k_p2p<T, F, 1>, 64, rest, N.n - rest);
-    else if (G == 2) launch(k_p2p<T, F, 2>, 64, rest, N.n - rest);
-    else launch(k_p2p<T, F, 4>, 64, rest, N.n - rest);
   };
-  if (field) all(std::true_type{});
-  else all(std::false_type{});
+  for (int k = 0; k < runs; ++k) {
+    if (run[k].count == 0) continue;
+    if (field) all(run[k], std::true_type{});
+    else all(run[k], std::false_type{});
+  }
   if (N.n_split > 0) {
     auto sum = [&](auto kern) {
       // a block per 64 columns of the largest leaf (others loop or idle)
@@ -618,3 +640,19 @@ void near_field(fmm_plan* pl, const ListSet& Ls, const void* src, int64_t n, voi
 }
 
 }  // namespace fmm
+
+// For the tests, no part of the ABI: the forms of a pass as threads of an
+// item's block (0: one wave, one target a lane) and the items of each, up to
+// four; returns their number.
+extern "C" int fmm_near_runs(const fmm_plan* pl, int transposed, int field, int* threads,
+                             int64_t* items) {
+  using namespace fmm;
+  NearRun run[4];
+  const int k = near_runs(pl, pl->lists[transposed ? 1 : 0], field != 0, run);
+  for (int j = 0; j < k; ++j) {
+    const int f = run[j].form;
+    threads[j] = f == kNearWide256 ? 256 : f == kNearWide ? 128 : f == kNearWide64 ? 64 : 0;
+    items[j] = run[j].count;
+  }
+  return k;
+}
