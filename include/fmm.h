@@ -350,13 +350,13 @@ fmm_status fmm_plan_read_profile(fmm_plan* plan, double* stage_ms,
                                  int64_t* passes);
 
 /* Choose the launch tiles of the single-vector evaluation (fmm_tiles) by
- * timing them on this plan: first the M2L form, the M2M / L2L form (one
- * lane or several waves per translation) and the near field's stream, then
- * the number of source groups of the near-field kernel (1, 2 or 4) together
- * with the number of leaves per wave of P2M and L2P (1, 2, 4 or 8), among
- * the values the plan's largest leaf allows; on plans of the 32-vector form
- * (FP32, max_rhs > 1) also the batched near field's waves per block, timed
- * on passes of max_rhs copies of q.  Every candidate runs one untimed and
+ * timing them on this plan: first the M2L form (where both are built, see
+ * m2l_waves), the M2M / L2L form (one lane or several waves per translation)
+ * and the near field's stream, then the number of source groups of the
+ * near-field kernel (1, 2 or 4) together with the number of leaves per wave
+ * of P2M and L2P (1, 2, 4 or 8), among the values the plan's largest leaf
+ * allows; on plans of the 32-vector form (FP32, max_rhs > 1) also the batched
+ * near field's waves per block, timed on passes of max_rhs copies of q.  Every candidate runs one untimed and
  * three timed evaluations of the charges q (device, [n], the plan's
  * precision) on `stream`; the fastest values are stored in the plan
  * and used by every later evaluation (results change only by the summation

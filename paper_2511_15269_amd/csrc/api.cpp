@@ -940,7 +940,8 @@ fmm_status fmm_plan_autotune(fmm_plan* pl, const void* q, void* stream, int* gro
         FMM_HIP(hipEventElapsedTime(&ms, e0, e1));
         return ms;
       };
-      if (m2l_share_waves(pl->prm.p, pl->prm.precision == FMM_FP64) > 1) {
+      // (elsewhere both values run the same kernel: the caller's stays)
+      if (m2l_shared_built(pl->prm.p, pl->prm.precision == FMM_FP64)) {
         pl->m2l_waves = 1;
         const float one = time3();
         pl->m2l_waves = 0;

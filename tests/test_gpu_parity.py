@@ -724,3 +724,37 @@ def test_split_near_field_lists_match_oracle(fmm, prec, n, p, leaf, s, theta):
     bound = 1e-10 if prec == "fp64" else 1e-5
     assert _rel(u.cpu().numpy(), u0) <= bound and _rel(f.cpu().numpy(), f0) <= bound
     assert torch.equal(u, v)
+
+
+@pytest.mark.parametrize("prec,p", [("fp64", 6), ("fp64", 7), ("fp32", 9), ("fp64", 8)])
+def test_autotune_leaves_a_tile_that_chooses_nothing(fmm, prec, p):
+    """Where both m2l_waves values run the same kernel, tuning keeps the
+    caller's value instead of the quicker of two equal timings."""
+    _say(f"[autotune] {prec} p={p}: one M2L form")
+    pos, q = workloads.uniform_cube(4000, 83)
+    dt = torch.float64 if prec == "fp64" else torch.float32
+    pt, qt = torch.from_numpy(pos).cuda(), torch.from_numpy(q).cuda().to(dt)
+    for k in range(4):
+        for waves in (0, 1):
+            plan = fmm.Plan(pt, p=p, leaf_max=64, splits=2, theta=0.6, precision=prec)
+            default = plan.tiles()["m2l_waves"]
+            plan.set_tiles(m2l_waves=waves)
+            assert plan.autotune(qt)["m2l_waves"] == (1 if waves else default)
+
+
+# the shared M2L form is built for FP32 at p = 10
+@pytest.mark.parametrize("kind", ["cube", "clustered"])
+@pytest.mark.parametrize("n,leaf,s,theta", [(900, 8, 1, 0.7), (26000, 40, 2, 0.8),
+                                            (30000, 64, 3, 0.5)])
+def test_m2l_shared_form_at_its_order(fmm, kind, n, leaf, s, theta):
+    _say(f"[m2l forms] fp32 p=10 {kind} n={n} leaf={leaf} s={s} theta={theta}")
+    pos, q = (workloads.uniform_cube if kind == "cube" else workloads.clustered)(n, 91)
+    plan = fmm.Plan(torch.from_numpy(pos).cuda(), p=10, leaf_max=leaf, splits=s, theta=theta,
+                    precision="fp32")
+    qt = torch.from_numpy(q).cuda().float()
+    assert plan.tiles()["m2l_waves"] == 4
+    four = [*plan.evaluate(qt), *plan.evaluate_transposed(qt)]
+    plan.set_tiles(m2l_waves=1)
+    one = [*plan.evaluate(qt), *plan.evaluate_transposed(qt)]
+    for a, b in zip(four, one):
+        assert torch.equal(a, b)
