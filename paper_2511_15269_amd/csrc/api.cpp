@@ -409,6 +409,7 @@ void check_device(const fmm_plan* pl) {
 // (p = 4) to 226 | 2400 | 3681 (p = 10), 2^18 300 | 1732 | 2536.
 constexpr int kFewVectors = 5, kFewVectorsSmall = 3;
 constexpr int64_t kFewVectorsPoints = 1 << 14;
+int few_vectors(int64_t n) { return n < kFewVectorsPoints ? kFewVectorsSmall : kFewVectors; }
 
 void run_vectors(fmm_plan* pl, int dir, const void* q, int nrhs, void* pot, void* field,
                  hipStream_t st) {
@@ -420,7 +421,7 @@ void run_vectors(fmm_plan* pl, int dir, const void* q, int nrhs, void* pot, void
       const float* qr = (const float*)q + (int64_t)r0 * n;
       float* ur = (float*)pot + (int64_t)r0 * n;
       float* fr = field ? (float*)field + 3 * (int64_t)r0 * n : nullptr;
-      if (R <= (n < kFewVectorsPoints ? kFewVectorsSmall : kFewVectors))
+      if (R <= few_vectors(n))
         evaluate(pl, pl->ws, dir, qr, R, ur, fr, st);
       else
         evaluate_batch(pl, dir, qr, R, ur, fr, st);
@@ -980,9 +981,10 @@ fmm_status fmm_plan_autotune(fmm_plan* pl, const void* q, void* stream, int* gro
       }
       pl->p2p_groups = bg;
       pl->leaves_per_wave = bl;
-      if (batched_plan(pl) && pl->ws.bq) {
+      const int R = std::min(pl->prm.max_rhs, batch_width());
+      // (plans of fewer vectors never run the 32-vector pass)
+      if (batched_plan(pl) && pl->ws.bq && R > few_vectors(pl->n)) {
         // the 32-vector pass on max_rhs copies of q
-        const int R = std::min(pl->prm.max_rhs, batch_width());
         const size_t row = sizeof(float) * (size_t)pl->n;
         qb = dev_alloc(pl, row * R);
         pb = dev_alloc(pl, row * R);

@@ -742,6 +742,18 @@ def test_autotune_leaves_a_tile_that_chooses_nothing(fmm, prec, p):
             assert plan.autotune(qt)["m2l_waves"] == (1 if waves else default)
 
 
+def test_autotune_leaves_the_many_vector_tile_of_few_vector_plans(fmm):
+    """Plans whose vectors are always taken one by one never run the
+    32-vector near field: tuning does not time it."""
+    _say("[autotune] two vectors")
+    pos, q = workloads.uniform_cube(3000, 84)
+    pt, qt = torch.from_numpy(pos).cuda(), torch.from_numpy(q).cuda().float()
+    for waves in (1, 2, 4, 8):
+        plan = fmm.Plan(pt, p=4, leaf_max=64, splits=2, theta=0.6, precision="fp32", max_rhs=2)
+        plan.set_tiles(batch_p2p_waves=waves)
+        assert plan.autotune(qt)["batch_p2p_waves"] == waves
+
+
 # the shared M2L form is built for FP32 at p = 10
 @pytest.mark.parametrize("kind", ["cube", "clustered"])
 @pytest.mark.parametrize("n,leaf,s,theta", [(900, 8, 1, 0.7), (26000, 40, 2, 0.8),
