@@ -307,7 +307,9 @@ struct Scratch {
   std::vector<void*> ptrs;
   Arena arena;
   size_t block;  // size of the next block
-  explicit Scratch(fmm_plan* p, size_t expect = 0) : pl(p), block(((size_t)4 << 20) + expect) {}
+  // (a multiple of a piece's 256 bytes, so that a request of up to a block fits)
+  explicit Scratch(fmm_plan* p, size_t expect = 0)
+      : pl(p), block((((size_t)4 << 20) + expect + 255) / 256 * 256) {}
   void* get(size_t bytes) {
     bytes = bytes ? bytes : 16;
     if (!pl->allocator.alloc) {
