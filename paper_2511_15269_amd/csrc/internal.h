@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <exception>
 #include <new>
@@ -301,29 +302,48 @@ void plan_free_all(fmm_plan* pl);
 void* dev_alloc(fmm_plan* pl, size_t bytes);
 void dev_free(fmm_plan* pl, void* p);
 // Temporaries of one build step, released when it goes out of scope.  Taken
-// in blocks of growing size (one by one from a caller's allocator).
+// in blocks, to save calls of hipMalloc (one by one from a caller's allocator):
+// the first of the bytes that the step expects to need, later ones each twice
+// as large up to kStep.  The largest plan that fits must not shrink for it:
+// beyond kExpect nothing is taken in advance, requests above kOwn that do not
+// fit the first block are allocations of their own (so that a later block
+// leaves at most a quarter unused), and where the device has no room for a
+// block the request alone is tried.
 struct Scratch {
+  static constexpr size_t kFirst = (size_t)4 << 20, kOwn = (size_t)16 << 20,
+                          kStep = (size_t)64 << 20, kExpect = (size_t)1 << 30;
   fmm_plan* pl;
   std::vector<void*> ptrs;
   Arena arena;
   size_t block;  // size of the next block
   // (a multiple of a piece's 256 bytes, so that a request of up to a block fits)
   explicit Scratch(fmm_plan* p, size_t expect = 0)
-      : pl(p), block((((size_t)4 << 20) + expect + 255) / 256 * 256) {}
+      : pl(p), block((kFirst + (expect <= kExpect ? expect : 0) + 255) / 256 * 256) {}
   void* get(size_t bytes) {
     bytes = bytes ? bytes : 16;
     if (!pl->allocator.alloc) {
       if (void* p = arena.take(bytes)) return p;
-      if (bytes <= block) {
-        arena = Arena{(char*)dev_alloc(pl, block), block};
-        ptrs.push_back(arena.at);
-        block *= 2;
-        return arena.take(bytes);
-      }
+      if (bytes <= (ptrs.empty() ? block : std::min(block, kOwn)))
+        if (void* b = try_block()) {
+          arena = Arena{(char*)b, block};
+          block = std::min(2 * block, kStep);
+          return arena.take(bytes);
+        }
     }
     void* p = dev_alloc(pl, bytes);
     ptrs.push_back(p);
     return p;
+  }
+  // a block, or NULL where there is no room for it
+  void* try_block() {
+    try {
+      void* b = dev_alloc(pl, block);
+      ptrs.push_back(b);
+      return b;
+    } catch (const Error&) {
+      block = kFirst;
+      return nullptr;
+    }
   }
   ~Scratch() {
     // the build's kernels may still read them: wait for the stream first

@@ -74,13 +74,40 @@ int main() {
     for (size_t less : {0, 1, 100, 255, 256, 300})
       all = all && fits((size_t)1 << 50, e, {4 * MB + e - less, 5});
   std::printf("whole block: %d\n", (int)all);
+  // lists of a level march: ten arrays a level, the last levels the largest,
+  // three times what was expected in all
+  std::vector<size_t> march;
+  for (size_t level = 1; level <= 10; ++level)
+    for (int k = 0; k < 10; ++k) march.push_back(((size_t)3 << level) * MB / 16 + 4);
+  auto sum = [](const std::vector<size_t>& v) {
+    size_t s = 0;
+    for (size_t b : v) s += (b + 255) / 256 * 256;
+    return s;
+  };
+  for (size_t f : {(size_t)1, (size_t)16, (size_t)256}) {
+    std::vector<size_t> v;
+    for (size_t b : march) v.push_back(b * f);
+    const size_t need = sum(v);
+    std::printf("march %zu: %d", need / MB, (int)fits(need + need / 8 + 64 * MB, need / 3, v));
+    fits((size_t)1 << 50, need / 3, v);
+    std::printf(" peak %zu calls %zu\n", peak / MB, calls);
+  }
+  // a build whose expected block is larger than what it needs, and larger than
+  // the device
+  std::printf("over: %d", (int)fits(100 * MB, 800 * MB, {30 * MB, 30 * MB, 30 * MB}));
+  std::printf(" %d", (int)fits(1000 * MB, 40000 * MB, {300 * MB, 300 * MB, 300 * MB}));
+  // small requests right after an expected block that does not fit
+  std::printf(" %d\n", (int)fits(3 * MB, 800 * MB, {MB, 100, MB, 200}));
+  // ordinary builds: one block where the expectation holds
+  fits((size_t)1 << 50, 16 * MB, {5 * MB, 4 * MB, 3 * MB, 1 * MB, 100, 7});
+  std::printf("ordinary calls %zu\n", calls);
   return 0;
 }
 """
 
 
 @pytest.mark.skipif(GXX is None, reason="no g++")
-def test_build_temporaries(tmp_path):
+def test_build_temporaries_fit_where_their_sum_fits(tmp_path):
     src, exe = tmp_path / "scratch.cpp", tmp_path / "scratch"
     src.write_text(SOURCE)
     subprocess.run([GXX, "-std=c++17", "-O1", "-Wno-unused", "-D__HIP_PLATFORM_AMD__",
@@ -92,3 +119,12 @@ def test_build_temporaries(tmp_path):
     lines = out.splitlines()
     assert not {"OVERLAP", "LEAK", "NULL"} & set(lines)
     assert lines.pop(0) == "whole block: 1"
+    for line, factor in zip(lines[:3], (1, 16, 256)):
+        words = line.replace(":", "").split()
+        need, ok, peak = int(words[1]), int(words[2]), int(words[4])
+        # all temporaries that fit into 8/9 of the device are given
+        assert ok == 1
+        assert peak <= need * 9 / 8 + 64
+        assert int(words[6]) <= 100
+    assert lines[3] == "over: 1 1 1"
+    assert lines[4] == "ordinary calls 1"
