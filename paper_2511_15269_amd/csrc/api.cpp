@@ -51,6 +51,7 @@ void dev_free(fmm_plan* pl, void* p) {
 }
 
 void* plan_alloc(fmm_plan* pl, size_t bytes) {
+  if (pl->memory) return plan_alloc(pl->memory, bytes);
   bytes = bytes ? bytes : 16;
   if (!pl->allocator.alloc)
     if (void* p = pl->arena.take(bytes)) return p;
@@ -547,13 +548,17 @@ fmm_status fmm_multi_plan_create_ex(const double* pos, const int64_t* offsets, i
     std::vector<std::unique_ptr<fmm_plan>> subs;
     std::unique_ptr<fmm_plan> pl(new fmm_plan());
     use_allocator(pl.get(), allocator, st, flags);
+    // the problems' own trees and lists, in blocks shared by all of them
+    fmm_plan hold;
+    use_allocator(&hold, allocator, st);
     auto free_subs = [&] {
-      for (auto& u : subs) plan_free_all(u.get());
+      plan_free_all(&hold);
       subs.clear();
     };
     try {
       for (int k = 0; k < nprob; ++k) {
         subs.emplace_back(new fmm_plan());
+        subs.back()->memory = &hold;
         use_allocator(subs.back().get(), allocator, st);
         build_structure(subs.back().get(), pos + 3 * offsets[k], offsets[k + 1] - offsets[k], prm,
                         st);

@@ -267,6 +267,7 @@ struct fmm_plan {
 
   std::vector<fmm::DevBuf> bufs;
   fmm::Arena arena;  // small arrays (plans with a caller's allocator: none)
+  fmm_plan* memory = nullptr;  // plan whose blocks this one's arrays are part of
   size_t device_bytes = 0;
   // device memory source of the plan (fmm_plan_create_ex), also used for
   // temporaries during the build; stream passed to the callbacks

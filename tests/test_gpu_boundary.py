@@ -129,3 +129,35 @@ def test_allocator_failure_returns_everything(fmm):
         assert st == L.FMM_ENOMEM
         assert out.value == 4321
         assert tr.live == {}
+
+
+def test_many_small_problems_build_within_what_they_hold(fmm):
+    """A set of small problems is built in about the memory that its arrays
+    take, not in a block of its own for every problem."""
+    import threading
+    import time
+    k, n = 600, 50
+    _say(f"[memory] {k} problems of {n} points")
+    pos, _ = workloads.uniform_cube(k * n, 6)
+    P = torch.from_numpy(pos).cuda()
+    kw = dict(p=2, leaf_max=64, splits=2, theta=0.6)
+    fmm.Plan(P[:n], **kw)  # the library's own first allocations
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    low, done = [free0], threading.Event()
+
+    def watch():
+        while not done.is_set():
+            low[0] = min(low[0], torch.cuda.mem_get_info()[0])
+            time.sleep(0.002)
+
+    t = threading.Thread(target=watch)
+    t.start()
+    try:
+        plan = fmm.Plan(P, sizes=[n] * k, **kw)
+    finally:
+        done.set()
+        t.join(30)
+    peak = free0 - low[0]
+    _say(f"    peak {peak / 2**20:.0f} MiB, the plan holds {plan.info()['device_bytes'] / 2**20:.0f}")
+    assert peak <= 100 << 20
