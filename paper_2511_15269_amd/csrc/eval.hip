@@ -662,7 +662,7 @@ void run_pass(fmm_plan* pl, const Workspace& ws, int dir, const T* q, T* pot, T*
   const ListSet& Ls = pl->lists[dir];
   const Side& SS = src_side(pl, dir);  // charges: P2M, M2M
   const Side& TS = tgt_side(pl, dir);  // evaluation points: L2L, P2P, L2P
-  StageMarks mk(pl);
+  StageMarks mk(pl, ws.stages);
   // the sort stage (charges into leaf-ordered source records) is folded
   // into P2M; its timing slot stays empty
   mk.begin(kStSort, st);

@@ -110,3 +110,24 @@ def test_noalloc_rejects_plans_beyond_the_limit(L):
         assert bool(torch.all(pot == 7.0))  # outputs untouched
     finally:
         lib.fmm_plan_destroy(h)
+
+
+def test_noalloc_records_no_stage_profile(L):
+    """Stage times would need events, which are device-side allocations:
+    passes through the no-allocation entry point record none."""
+    _say("[noalloc] profiling on")
+    lib = L.lib()
+    pos, q = workloads.uniform_cube(3000, 4)
+    P, Q = torch.from_numpy(pos).cuda(), torch.from_numpy(q).cuda()[None].contiguous()
+    h = _create(L, P, "fp64", 0)
+    try:
+        assert lib.fmm_plan_set_profiling(h, 1) == L.FMM_OK
+        ms, passes = (ctypes.c_double * 7)(), ctypes.c_int64(-1)
+        _eval(L, lib.fmm_evaluate_noalloc, h, Q, 3000, torch.float64)
+        assert lib.fmm_plan_read_profile(h, ms, ctypes.byref(passes)) == L.FMM_OK
+        assert passes.value == 0 and not any(ms)
+        _eval(L, lib.fmm_evaluate, h, Q, 3000, torch.float64)
+        assert lib.fmm_plan_read_profile(h, ms, ctypes.byref(passes)) == L.FMM_OK
+        assert passes.value == 1 and all(t > 0 for t in ms[1:])
+    finally:
+        lib.fmm_plan_destroy(h)
