@@ -99,7 +99,9 @@ typedef struct {
   int64_t n_m2l;        /* multipole-to-local pairs (all levels)           */
   int64_t n_p2p;        /* leaf-leaf direct pairs (including self pairs)   */
   int64_t p2p_interactions; /* sum over direct pairs of |src| * |tgt|     */
-  int64_t device_bytes; /* device memory held by the plan (all of it)      */
+  int64_t device_bytes; /* device memory held by the plan (all of it; without
+                           a caller's allocator small arrays share blocks of
+                           1 MB, then 4 MB, which count whole)             */
   int64_t workspace_bytes; /* of which the evaluation workspace (see
                               fmm_plan_workspace_bytes)                    */
   int64_t p2p_items;    /* near-field work items (long direct lists are

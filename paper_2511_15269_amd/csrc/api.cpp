@@ -407,7 +407,11 @@ void check_device(const fmm_plan* pl) {
 // pass costs the same for 1 to 16 and for 17 to 32 vectors; measured, one
 // vector alone | 16 | 32 together: 4000 points 71 | 243 | 296 us, 30000 131 |
 // 715 | 1007 (p = 6) and 135 | 970 | 1400 (p = 8), 130000 111 | 523 | 726
-// (p = 4) to 226 | 2400 | 3681 (p = 10), 2^18 300 | 1732 | 2536.
+// (p = 4) to 226 | 2400 | 3681 (p = 10), 2^18 300 | 1732 | 2536.  So the two
+// cost the same at 3.4 vectors (4000 points), 4.7 (130000, p = 4), 5.5 and 7.2
+// (30000, p = 6, 8), 5.8 (2^18) and 10.6 (130000, p = 10); the line is one for
+// all orders, near the low ones' (5 vectors at p = 4 are 6% slower than
+// together, 6 to 10 at p = 10 would be quicker one by one).
 constexpr int kFewVectors = 5, kFewVectorsSmall = 3;
 constexpr int64_t kFewVectorsPoints = 1 << 14;
 int few_vectors(int64_t n) { return n < kFewVectorsPoints ? kFewVectorsSmall : kFewVectors; }

@@ -324,9 +324,9 @@ void run_batch(fmm_plan* pl, const ListSet& Ls, const float* q, int R, float* po
   mk.end(kStM2M, st);
   mk.begin(kStM2L, st);
   if (Ls.n_items > 0)
-    k_bm2l<P><<<blocks(Ls.n_items, 64 / cols), 64, 0, st>>>(cols, Ls.n_items, Ls.item_tgt, Ls.item_begin,
-                                                    Ls.item_end, Ls.m2l_src, pl->cx, pl->cy,
-                                                    pl->cz, pl->scale, C, tab, part);
+    k_bm2l<P><<<blocks(Ls.n_items, 64 / cols), 64, 0, st>>>(
+        cols, Ls.n_items, Ls.item_tgt, Ls.item_begin, Ls.item_end, Ls.m2l_src, pl->cx, pl->cy,
+        pl->cz, pl->scale, C, tab, part);
   mk.end(kStM2L, st);
   mk.begin(kStL2L, st);
   const Step& all = pl->side[0].l2l_sum;
@@ -334,8 +334,8 @@ void run_batch(fmm_plan* pl, const ListSet& Ls, const float* q, int R, float* po
     k_psum<float><<<(unsigned)all.n, 256, 0, st>>>(all.n, all.a, Ls.item_first, Ls.item_cnt,
                                                    part, K_<P>::value * kRB, D);
   for (const Step& S : pl->side[0].l2l_steps)
-    k_bl2l<P><<<blocks(S.n, 64 / cols), 64, 0, st>>>(cols, S.n, S.a, S.b, pl->cx, pl->cy, pl->cz, pl->scale,
-                                             tab, D);
+    k_bl2l<P><<<blocks(S.n, 64 / cols), 64, 0, st>>>(cols, S.n, S.a, S.b, pl->cx, pl->cy, pl->cz,
+                                                     pl->scale, tab, D);
   mk.end(kStL2L, st);
   mk.begin(kStL2P, st);
   k_bl2p<P><<<(unsigned)pl->nleaf, 256, 0, st>>>(pl->leaf_box, pl->leaf_start, pl->xs, pl->ys,

@@ -62,16 +62,16 @@ __global__ __launch_bounds__(256) void k_bgather(int64_t n, int R,
 // column l % 16 (+16 in the second half).  Source points (positions and the
 // 32 charges) are staged in LDS, up to kStage points at a time, with
 // coalesced loads.  A block holds TW waves, one 16-target tile each, that
-// share every staged chunk.  H: column halves, 1 for up to 16 vectors.  Small tiles keep the accumulators to 32
-// registers per lane; the kernel is held to three waves per SIMD (146
-// registers, no spills), so that the kernel values of one wave's next step
-// are computed while another wave's MFMAs run.  Bound by issue: the MFMAs take
-// 58% of the SIMDs' cycles and the vector instructions, which do not overlap
-// them, the rest.  So the leaf sums go to FP64 running sums (two instructions
-// an element; compensated FP32 sums took eight, 16 of the 39 vector
-// instructions a step) and distance 0 is looked for only in the target leaf
-// itself, or everywhere when some points cannot be told apart.  Measured (2^18 points, 64 a
-// leaf, theta = 0.8): 32 vectors 1.37 -> 1.26 ms.
+// share every staged chunk.  H: column halves, 1 for up to 16 vectors.  Small
+// tiles keep the accumulators to 32 registers per lane; the kernel is held to
+// three waves per SIMD (146 registers, no spills), so that the kernel values of
+// one wave's next step are computed while another wave's MFMAs run.  Bound by
+// issue: the MFMAs take 58% of the SIMDs' cycles and the vector instructions,
+// which do not overlap them, the rest.  So the leaf sums go to FP64 running sums
+// (two instructions an element; compensated FP32 sums took eight, 16 of the 39
+// vector instructions a step) and distance 0 is looked for only in the target
+// leaf itself, or everywhere when some points cannot be told apart.  Measured
+// (2^18 points, 64 a leaf, theta = 0.8): 32 vectors 1.37 -> 1.26 ms.
 constexpr int kStage = 64;
 
 template <int TW, int H>
@@ -259,8 +259,8 @@ void batch_near(const fmm_plan* pl, const ListSet& Ls, int R, const float* qL, f
   const int TW = batch_p2p_waves(pl);
   auto p2p = [&](auto kern, int tw) {
     kern<<<(unsigned)pl->nleaf, 64 * tw, 0, st>>>(pl->leaf_start, pl->xs, pl->ys, pl->zs, qL,
-                                                   Ls.p2p_ptr, Ls.p2p_src, pl->has_dup ? 1 : 0, potL,
-                                                   fldL);
+                                                   Ls.p2p_ptr, Ls.p2p_src, pl->has_dup ? 1 : 0,
+                                                   potL, fldL);
   };
   auto all = [&](auto halves) {
     constexpr int H = decltype(halves)::value;

@@ -378,7 +378,8 @@ __global__ __launch_bounds__(kM2LBlock* W)
   // pairs of the longest item of the block (the same in every wave)
   int longest = len;
 #pragma unroll
-  for (int off = 1; off < kM2LBlock; off <<= 1) longest = max(longest, __shfl_xor(longest, off, 64));
+  for (int off = 1; off < kM2LBlock; off <<= 1)
+    longest = max(longest, __shfl_xor(longest, off, 64));
   longest = __builtin_amdgcn_readfirstlane(longest);
   for (int j = w; j - w < longest; j += W) {
     // lanes past their item's end translate its last pair (or the list's

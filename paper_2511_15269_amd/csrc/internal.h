@@ -58,7 +58,7 @@ struct Arena {
 
 // Constant operator tables of one expansion order (values in double; the
 // float path keeps a rounded copy).  Layouts are shared with the kernels in
-// eval.hip through the index helpers of tables.h.
+// eval.hip and batch.hip through the index helpers of tables.h.
 struct Tables {
   int p = -1;
   std::vector<double> host;  // all tables, concatenated
@@ -306,11 +306,12 @@ void dev_free(fmm_plan* pl, void* p);
 // in blocks, to save calls of hipMalloc and hipFree (one by one from a caller's
 // allocator): the first of the bytes that the step expects to need, later ones
 // each twice as large up to kStep (blocks of 64 MB and allocations of their own
-// above 16 MB: plan of 2^20 points 19.0 -> 19.8 ms, destroyed 1.4 -> 1.9).  The largest plan that fits
-// must not shrink for it: beyond kExpect nothing is taken in advance, requests
-// above kOwn that do not fit the first block are allocations of their own (so
-// that a later block leaves at most a quarter unused), and where the device has
-// no room for a block the request alone is tried.
+// above 16 MB: plan of 2^20 points 19.0 -> 19.8 ms, destroyed 1.4 -> 1.9).  The
+// largest plan that fits must not shrink for it: beyond kExpect nothing is taken
+// in advance, requests above kOwn that do not fit the first block are
+// allocations of their own (so that a later block leaves at most a quarter
+// unused), and where the device has no room for a block the request alone is
+// tried.
 struct Scratch {
   static constexpr size_t kFirst = (size_t)4 << 20, kOwn = (size_t)256 << 20,
                           kStep = (size_t)1 << 30, kExpect = (size_t)1 << 30;
@@ -423,7 +424,7 @@ inline bool batched_plan(const fmm_plan* pl) {
 void make_work(fmm_plan* pl, int dir, hipStream_t st);
 // Operator tables for order p (tables.cpp), cached per process/device.
 const void* get_tables(int p, int precision, int device);
-// Evaluation (eval.hip): dir 0 = G-hat, dir 1 = G-hat^T.
+// Evaluation (pass.hip): dir 0 = G-hat, dir 1 = G-hat^T.
 void evaluate(fmm_plan* pl, const Workspace& ws, int dir, const void* q, int nrhs, void* pot,
               void* field, hipStream_t st);
 // Up to kBatchWidth FP32 charge vectors in one pass (batch.hip, compiled once
@@ -444,7 +445,7 @@ int batch_p2p_waves(const fmm_plan* pl);
 void make_iperm(fmm_plan* pl, hipStream_t st);
 void evaluate_batch(fmm_plan* pl, int dir, const float* q, int R, float* pot, float* field,
                     hipStream_t st);
-// Adjoint combine: grad_x = -(g * field_fwd + q * field_t) (eval.hip).
+// Adjoint combine: grad_x = -(g * field_fwd + q * field_t) (pass.hip).
 void adjoint_combine(fmm_plan* pl, const void* q, const void* g, const void* field_fwd,
                      const void* field_t, void* grad_x, hipStream_t st);
 
@@ -452,7 +453,7 @@ void adjoint_combine(fmm_plan* pl, const void* q, const void* g, const void* fie
 void direct_sum(int64_t n, const double* pos, const void* q, int precision,
                 const int64_t* targets, int64_t nt, void* pot, void* field,
                 hipStream_t st);
-// Launch tiles in effect (eval.hip): P2P source groups G (1, 2, 4; G > 1
+// Launch tiles in effect (pass.hip): P2P source groups G (1, 2, 4; G > 1
 // needs max_leaf_count <= 64 / G) and P2M/L2P leaves per wave (1, 2, 4, 8;
 // needs max_leaf_count <= 64 / leaves).
 int p2p_groups(const fmm_plan* pl);

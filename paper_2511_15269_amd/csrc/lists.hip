@@ -431,7 +431,8 @@ void build_lists(fmm_plan* pl, const TreeDesc& ts, const TreeDesc& tt, hipStream
     std::vector<double> c(6);
     for (int a = 0; a < 3; ++a) {
       double* arr[3] = {pl->cx, pl->cy, pl->cz};
-      FMM_HIP(hipMemcpyAsync(&c[a], arr[a] + ts.box_base, sizeof(double), hipMemcpyDeviceToHost, st));
+      FMM_HIP(hipMemcpyAsync(&c[a], arr[a] + ts.box_base, sizeof(double),
+                             hipMemcpyDeviceToHost, st));
       FMM_HIP(hipMemcpyAsync(&c[3 + a], arr[a] + tt.box_base, sizeof(double),
                              hipMemcpyDeviceToHost, st));
     }
