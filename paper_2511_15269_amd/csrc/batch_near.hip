@@ -66,12 +66,12 @@ __global__ __launch_bounds__(256) void k_bgather(int64_t n, int R,
 // tiles keep the accumulators to 32 registers per lane; the kernel is held to
 // three waves per SIMD (146 registers, no spills), so that the kernel values of
 // one wave's next step are computed while another wave's MFMAs run.  Bound by
-// issue: the MFMAs take 58% of the SIMDs' cycles and the vector instructions,
+// issue: the MFMAs take 56% of the SIMDs' cycles and the vector instructions,
 // which do not overlap them, the rest.  So the leaf sums go to FP64 running sums
 // (two instructions an element; compensated FP32 sums took eight, 16 of the 39
 // vector instructions a step) and distance 0 is looked for only in the target
 // leaf itself, or everywhere when some points cannot be told apart.  Measured
-// (2^18 points, 64 a leaf, theta = 0.8): 32 vectors 1.37 -> 1.26 ms.
+// (2^18 points, 64 a leaf, theta = 0.8): 32 vectors 1.29 -> 1.20 ms.
 constexpr int kStage = 64;
 
 template <int TW, int H>

@@ -355,8 +355,10 @@ constexpr int m2l_waves_per_simd(int p, bool fp64) {
 // in the translation steps) give two waves in FP64 at p = 8 (81 x 63
 // accumulators of 8 bytes, 40 KB for two waves) and four in FP32, where one
 // wave per accumulator set gave one and two.  Measured (uniform cube 2^20,
-// 3.4 M pairs, p = 8): FP64 0.55 -> 0.45 ms, FP32 0.36 (one wave per
-// accumulator set, otherwise alike) -> 0.28 ms; W = 1 in FP64 0.53 ms.
+// 3.4 M pairs, p = 8; one wave per accumulator set before): FP64 0.50 -> 0.40
+// ms, FP32 0.29 -> 0.27 ms; 100000 points, FP32, p = 10 (four waves a
+// translation) 118 -> 91 us, but 2800 points 63.0 -> 63.5 us and M2M there 17.6
+// -> 18.2 us (without the pins in M2M's shares 17.9, the pass no shorter).
 template <int P, typename T, int W>
 __global__ __launch_bounds__(kM2LBlock* W)
     __attribute__((amdgpu_waves_per_eu(m2l_waves_per_simd(P, sizeof(T) == 8)))) void k_m2l(

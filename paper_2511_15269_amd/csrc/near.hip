@@ -14,7 +14,7 @@ using namespace ops;
 // One source point against the lane's target at (xi, yi, zi): the
 // difference is taken in FP64 and rounded to T.  In FP64 the Newton step
 // gives 2 / r, one operation less than 1 / r (near_scale takes the powers of
-// two out again: 17 instead of 18 operations).  SAFE: pairs at distance 0
+// two out again: 16 instead of 17 operations and the root).  SAFE: pairs at distance 0
 // contribute nothing (needed within a leaf, and between leaves when the
 // point set has points at a distance that is 0 in T); otherwise the pair is
 // known to be apart.
@@ -357,10 +357,10 @@ __global__ __launch_bounds__(W) __attribute__((amdgpu_waves_per_eu(4))) void k_p
 // but the groups share out the points of the item's source leaves (staged
 // one after another, group g takes every ng-th record) and every thread sums
 // all its points before the groups' sums are added once, so that neither
-// leaves nor lists leave groups idle.  Bound by VALU issue (17 FP64
+// leaves nor lists leave groups idle.  Bound by VALU issue (16 FP64
 // operations and the reciprocal square root a pair).  Measured (near field
 // against k_p2p with two or four groups): 384 charges and 2048 probes 33 ->
-// 13 us, uniform cube 2^20 (32 points a leaf) 0.64 -> 0.63 ms.
+// 13 us, uniform cube 2^20 (32 points a leaf) 0.59 -> 0.58 ms.
 template <bool FIELD, int W>
 __global__ __launch_bounds__(W) __attribute__((amdgpu_waves_per_eu(4))) void k_p2p_flat(
     int64_t n, int item0, const int32_t* __restrict__ item_leaf,
