@@ -359,8 +359,8 @@ fmm_status fmm_plan_read_profile(fmm_plan* plan, double* stage_ms,
  * of P2M and L2P (1, 2, 4 or 8), among the values the plan's largest leaf
  * allows; on plans of the 32-vector form (FP32, max_rhs > 1) also the batched
  * near field's waves per block, timed on passes of max_rhs copies of q (not
- * where max_rhs is so small that vectors are always taken one by one: up to
- * 5, up to 3 below 2^14 points).  Every candidate runs one untimed and
+ * on plans whose max_rhs vectors are taken one by one: few vectors, at most
+ * 5, where a pass for each is estimated to be quicker).  Every candidate runs one untimed and
  * three timed evaluations of the charges q (device, [n], the plan's
  * precision) on `stream`; the fastest values are stored in the plan
  * and used by every later evaluation (results change only by the summation
@@ -396,8 +396,7 @@ fmm_status fmm_plan_autotune(fmm_plan* plan, const void* q, void* stream, int* p
  *                    waves share every staged source chunk): 1, 2, 4 or 8;
  *                    by default set from the plan's largest leaf.  Identical
  *                    results.  Read and set on every plan; used by FP32
- *                    evaluations of more than 5 vectors (3 below 2^14
- *                    points).
+ *                    evaluations whose vectors are not taken one by one.
  *   near_stream      2 (default): the near field runs on a second stream
  *                    of the plan beside the far-field chain (M2M, M2L,
  *                    L2L), forked after P2M and joined before L2P; 1: every

@@ -401,21 +401,9 @@ void check_device(const fmm_plan* pl) {
     throw Error{FMM_EDEVICE, "current device differs from the plan's device"};
 }
 
-// Several charge vectors: FP32 plans built for more than one vector take
-// them kRB at a time through the multi-vector kernels; otherwise, and for the
-// few vectors that are quicker so, one pass per vector.  The multi-vector
-// pass costs the same for 1 to 16 and for 17 to 32 vectors; measured, one
-// vector alone | 16 | 32 together: 4000 points 71 | 243 | 296 us, 30000 131 |
-// 715 | 1007 (p = 6) and 135 | 970 | 1400 (p = 8), 130000 111 | 523 | 726
-// (p = 4) to 226 | 2400 | 3681 (p = 10), 2^18 300 | 1732 | 2536.  So the two
-// cost the same at 3.4 vectors (4000 points), 4.7 (130000, p = 4), 5.5 and 7.2
-// (30000, p = 6, 8), 5.8 (2^18) and 10.6 (130000, p = 10); the line is one for
-// all orders, near the low ones' (5 vectors at p = 4 are 6% slower than
-// together, 6 to 10 at p = 10 would be quicker one by one).
-constexpr int kFewVectors = 5, kFewVectorsSmall = 3;
-constexpr int64_t kFewVectorsPoints = 1 << 14;
-int few_vectors(int64_t n) { return n < kFewVectorsPoints ? kFewVectorsSmall : kFewVectors; }
-
+// Several charge vectors: FP32 plans built for more than one vector take them
+// kRB at a time through the multi-vector kernels, or one by one where that is
+// quicker (vectors_one_by_one); other plans take one pass per vector.
 void run_vectors(fmm_plan* pl, int dir, const void* q, int nrhs, void* pot, void* field,
                  hipStream_t st) {
   if (nrhs > 1 && pl->ws.bq) {
@@ -426,7 +414,7 @@ void run_vectors(fmm_plan* pl, int dir, const void* q, int nrhs, void* pot, void
       const float* qr = (const float*)q + (int64_t)r0 * n;
       float* ur = (float*)pot + (int64_t)r0 * n;
       float* fr = field ? (float*)field + 3 * (int64_t)r0 * n : nullptr;
-      if (R <= few_vectors(n))
+      if (vectors_one_by_one(pl, R))
         evaluate(pl, pl->ws, dir, qr, R, ur, fr, st);
       else
         evaluate_batch(pl, dir, qr, R, ur, fr, st);
@@ -991,8 +979,8 @@ fmm_status fmm_plan_autotune(fmm_plan* pl, const void* q, void* stream, int* gro
       pl->p2p_groups = bg;
       pl->leaves_per_wave = bl;
       const int R = std::min(pl->prm.max_rhs, batch_width());
-      // (plans of fewer vectors never run the 32-vector pass)
-      if (batched_plan(pl) && pl->ws.bq && R > few_vectors(pl->n)) {
+      // (plans of so few vectors never run the 32-vector pass)
+      if (batched_plan(pl) && pl->ws.bq && !vectors_one_by_one(pl, R)) {
         // the 32-vector pass on max_rhs copies of q
         const size_t row = sizeof(float) * (size_t)pl->n;
         qb = dev_alloc(pl, row * R);

@@ -441,6 +441,8 @@ void run_batch(fmm_plan* pl, const ListSet& Ls, const float* q, int R, float* po
                hipStream_t st);
 // waves per block of the batched near field for this plan
 int batch_p2p_waves(const fmm_plan* pl);
+// Whether R vectors (1 <= R <= kBatchWidth) are taken one by one.
+bool vectors_one_by_one(const fmm_plan* pl, int R);
 // iperm of a batched plan from its perm (on st)
 void make_iperm(fmm_plan* pl, hipStream_t st);
 void evaluate_batch(fmm_plan* pl, int dir, const float* q, int R, float* pot, float* field,

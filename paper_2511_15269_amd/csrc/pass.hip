@@ -1,5 +1,6 @@
 // One evaluation pass of a plan: the launch tiles in effect, the choice of
 // the order's kernels (eval.hip) and the adjoint's combine step.
+#include <algorithm>
 #include <cmath>
 
 #include "internal.h"
@@ -57,6 +58,42 @@ int near_form(const fmm_plan* pl, int nt, double list, int64_t items, bool field
     }
   }
   return form;
+}
+// A single-vector pass against the pass of up to 16 vectors, both in us as the
+// sum of what they wait for: launches, the level chains, M2L (the length of a
+// translation or the pairs' throughput), the near field (the length of a list
+// or its throughput) and the work per point.  The two were fitted to 474 plans
+// on the cube and the sphere: 60 to 260000 points, p = 2 to 10, leaves of 16 to
+// 256 points; each is within 20% of the measured time for nine plans in ten.
+// Vectors are taken one by one up to kFewVectors while that is estimated at most
+// 5% longer.  Against the better of the two ways as measured this loses less than
+// 1% on average for 2 to 5 vectors and 10 to 30% at worst; by count alone (3, or 5
+// from 2^14 points) it lost 16 to 39% on average, and small plans up to six times:
+// 3 vectors of 300 points, leaves of 32, 141 us one by one and 76 together; 5
+// vectors of 20000 points, p = 4, 288 and 226; 5 of 130000, p = 10, 1130 and 2400.
+bool vectors_one_by_one(const fmm_plan* pl, int R) {
+  constexpr int kFewVectors = 5, kFewVectorsSmall = 3;
+  constexpr int64_t kFewVectorsPoints = 1 << 14;
+  if (R == 1) return true;
+  if (R > (pl->n < kFewVectorsPoints ? kFewVectorsSmall : kFewVectors)) return false;
+  const double n = (double)pl->n, p = pl->prm.p, K = (p + 1) * (p + 1);
+  const double turn = p * p * std::sqrt(p);  // a translation's growth with p
+  const double pairs = (double)pl->lists[0].n_m2l, inter = (double)pl->p2p_inter;
+  const double far = pairs > 0 ? 1.0 : 0.0, levels = pl->L, list = inter / n;
+  const double leaf = std::ceil(n / (double)pl->nleaf);
+  const double tiles = std::ceil(leaf / (16.0 * batch_p2p_waves(pl)));
+  const double chain1 = levels * 0.071 * p * p +
+                        std::max(far * 0.074 * turn, pairs * 1e-6 * (41 + 0.42 * turn));
+  // (leaves of up to 32 points are swept by one wave, staged leaf by leaf)
+  const double near1 = std::max(leaf <= 32 ? 0.026 * list : 0.0, inter * 0.44e-6);
+  const double one = 58 + std::max(chain1, near1) + 0.5 * std::min(chain1, near1) +
+                     n * 2.4e-6 * K;
+  const double chain16 = far * levels * (9 + 0.24 * p * p);
+  const double m2l16 = std::max(far * (19 + 0.31 * turn) * std::min(1.0, pairs / 2500),
+                                pairs * 1e-6 * (240 + 10.5 * turn));
+  const double near16 = std::max(0.094 * list * tiles, inter * 1.9e-6);
+  const double together = 26 + 0.24 * K + chain16 + m2l16 + near16 + n * 1e-6 * (150 + 20 * K);
+  return R * one <= 1.05 * together;
 }
 int chain_waves(const fmm_plan* pl) {
   return pl->prm.p < kChainShareMinOrder || pl->chain_waves == 1 ? 1 : kShareWaves;

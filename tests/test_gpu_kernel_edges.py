@@ -179,3 +179,26 @@ def test_plans_made_and_dropped_share_no_state(fmm):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(ug, u0) and torch.equal(fg, f0)
+
+
+# a pass for each vector, or one for all: small plans and low orders take them
+# together, where a pass alone is short against the pass of many
+@pytest.mark.parametrize("n,leaf,s,p,R,passes", [
+    (60, 32, 2, 6, 2, 1), (300, 32, 2, 5, 2, 1), (300, 32, 2, 5, 3, 1), (3000, 64, 2, 8, 3, 3),
+    (3000, 64, 2, 8, 4, 1), (20000, 128, 3, 4, 5, 1), (20000, 128, 3, 4, 2, 2),
+    (130000, 64, 2, 10, 5, 5), (130000, 64, 2, 10, 6, 1), (130000, 64, 2, 10, 37, 6)])
+def test_few_vectors_take_the_quicker_way(fmm, n, leaf, s, p, R, passes):
+    _say(f"[few vectors] n={n} p={p} R={R}")
+    pos, _ = workloads.uniform_cube(n, 38)
+    Q = torch.from_numpy(np.random.default_rng(39).uniform(-1, 1, (R, n))).cuda().float()
+    plan = fmm.Plan(torch.from_numpy(pos).cuda(), p=p, leaf_max=leaf, splits=s, theta=0.7,
+                    precision="fp32", max_rhs=R)
+    U, Fd = plan.evaluate(Q)
+    plan.set_profiling(True)
+    u, f = plan.evaluate(Q)
+    assert plan.read_profile()[1] == passes
+    assert torch.equal(u, U) and torch.equal(f, Fd)
+    plan.set_profiling(False)
+    u1, f1 = plan.evaluate(Q[R - 1])
+    assert _rel(U[R - 1].double().cpu().numpy(), u1.double().cpu().numpy()) <= 1e-6
+    assert _rel(Fd[R - 1].double().cpu().numpy(), f1.double().cpu().numpy()) <= 1e-6
