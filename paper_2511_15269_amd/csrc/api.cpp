@@ -505,7 +505,7 @@ fmm_status fmm_plan_create_ex(const double* pos, int64_t n, const fmm_params* pr
     use_allocator(pl.get(), allocator, st, flags);
     try {
       build_structure(pl.get(), pos, n, prm, st);
-      for (int d = 0; d < 2; ++d) make_work(pl.get(), d, st);
+      make_work(pl.get(), st);
       make_steps(pl.get(), {{TreeDesc{pl->L, pl->level_off, 0, 0}}}, st);
       alloc_workspace(pl.get(), st);
       make_fork(pl.get());
@@ -625,7 +625,7 @@ fmm_status fmm_plan_create_st(const double* src, int64_t ns, const double* tgt, 
         pl->side[k].nleaf = sub[k]->nleaf;
       }
       build_lists(pl.get(), ts, tt, st);
-      for (int d = 0; d < 2; ++d) make_work(pl.get(), d, st);
+      make_work(pl.get(), st);
       make_steps(pl.get(), {{ts}, {tt}}, st);
       (void)hipStreamSynchronize(st);
       free_subs();

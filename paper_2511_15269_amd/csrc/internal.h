@@ -102,8 +102,8 @@ struct NearItems {
   int32_t* split_leaf = nullptr;
   int32_t* split_first = nullptr;
   int32_t* split_cnt = nullptr;
-  void* part = nullptr;
-  int64_t n = 0, n_split = 0;
+  void* part = nullptr;  // one buffer of both directions (make_work)
+  int64_t n = 0, n_split = 0, part_elems = 0;
   // items of leaves of the wide forms (near_form) come first, those of more
   // threads (256, 128, 64) before those of fewer
   int64_t n_wide256 = 0, n_wide = 0, n_wide64 = 0;
@@ -420,8 +420,8 @@ void build_lists(fmm_plan* pl, const TreeDesc& src, const TreeDesc& tgt, hipStre
 inline bool batched_plan(const fmm_plan* pl) {
   return pl->prm.precision == FMM_FP32 && pl->prm.max_rhs > 1 && pl->nsides == 1;
 }
-// Work distribution of direction dir (lists.hip): M2L items, near-field items.
-void make_work(fmm_plan* pl, int dir, hipStream_t st);
+// Work distribution of both directions (lists.hip): M2L items, near-field items.
+void make_work(fmm_plan* pl, hipStream_t st);
 // Operator tables for order p (tables.cpp), cached per process/device.
 const void* get_tables(int p, int precision, int device);
 // Evaluation (pass.hip): dir 0 = G-hat, dir 1 = G-hat^T.

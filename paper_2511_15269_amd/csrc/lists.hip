@@ -188,19 +188,27 @@ void make_items(fmm_plan* pl, ListSet& S, const std::vector<int32_t>& mptr, hipS
   const int item_pairs =
       (int)(fp64 ? std::min(std::max(S.n_m2l / kItemsFull, (int64_t)2), kItemPairs) : kItemPairs);
   std::vector<int32_t> tg, ni;  // targets with a list, in box order; their item counts
+  int64_t total = 0;
   for (int64_t t = 0; t < pl->nbox; ++t) {
     const int32_t lt = mptr[t + 1] - mptr[t];
     if (lt == 0) continue;
     tg.push_back((int32_t)t);
     ni.push_back(std::min((lt + item_pairs - 1) / item_pairs, lanes));
+    total += ni.back();
   }
+  // fewest items of any target from the k-th on: what a block has left for it
+  // not to be searched any further
+  std::vector<int32_t> fewest(ni);
+  for (size_t k = fewest.size(); k-- > 1;) fewest[k - 1] = std::min(fewest[k - 1], fewest[k]);
   std::vector<int32_t> it_t, it_b, it_e, first(pl->nbox, 0), cnt(pl->nbox, 0);
+  for (auto* v : {&it_t, &it_b, &it_e})
+    v->reserve((size_t)(total / lanes + 64) * 5 / 4 * kM2LBlock);
   std::vector<int32_t> seg_ptr(1, 0), seg_tgt, seg_lanes;
   std::vector<char> placed(tg.size(), 0);
   size_t j = 0;
   while (j < tg.size()) {
     int used = 0;
-    for (size_t k = j; k < tg.size() && k < j + kPackWindow && used < lanes; ++k) {
+    for (size_t k = j; k < tg.size() && k < j + kPackWindow && used + fewest[k] <= lanes; ++k) {
       if (placed[k] || used + ni[k] > lanes) continue;
       placed[k] = 1;
       const int32_t t = tg[k], lt = mptr[t + 1] - mptr[t];
@@ -208,18 +216,19 @@ void make_items(fmm_plan* pl, ListSet& S, const std::vector<int32_t>& mptr, hipS
       cnt[t] = ni[k];
       seg_tgt.push_back(t);
       seg_lanes.push_back(used | ((used + ni[k]) << 8));
-      for (int32_t q = 0; q < ni[k]; ++q) {
+      int32_t begin = mptr[t];
+      for (int32_t q = 1; q <= ni[k]; ++q) {
+        const int32_t end = mptr[t] + (int32_t)((int64_t)lt * q / ni[k]);
         it_t.push_back(t);
-        it_b.push_back(mptr[t] + (int32_t)((int64_t)lt * q / ni[k]));
-        it_e.push_back(mptr[t] + (int32_t)((int64_t)lt * (q + 1) / ni[k]));
+        it_b.push_back(begin);
+        it_e.push_back(end);
+        begin = end;
       }
       used += ni[k];
     }
-    for (; used < kM2LBlock; ++used) {
-      it_t.push_back(-1);
-      it_b.push_back(0);
-      it_e.push_back(0);
-    }
+    it_t.resize(it_t.size() + kM2LBlock - used, -1);
+    it_b.resize(it_t.size(), 0);
+    it_e.resize(it_t.size(), 0);
     seg_ptr.push_back((int32_t)seg_tgt.size());
     while (j < tg.size() && placed[j]) ++j;
   }
@@ -330,8 +339,7 @@ NearItems near_items(fmm_plan* pl, const Side& T, const std::vector<int32_t>& pt
   if (!out.empty())
     FMM_HIP(hipMemcpyAsync(N.out, out.data(), sizeof(int64_t) * out.size(), hipMemcpyHostToDevice,
                            st));
-  const size_t es = pl->prm.precision == FMM_FP32 ? sizeof(float) : sizeof(double);
-  N.part = part > 0 ? plan_alloc(pl, es * (size_t)part) : nullptr;
+  N.part_elems = part;
   FMM_HIP(hipStreamSynchronize(st));
   return N;
 }
@@ -354,22 +362,23 @@ void make_p2p_items(fmm_plan* pl, ListSet& S, const Side& T, const std::vector<i
     FMM_HIP(hipMemcpyAsync(src.data(), S.p2p_src, sizeof(int32_t) * S.n_p2p,
                            hipMemcpyDeviceToHost, st));
   FMM_HIP(hipStreamSynchronize(st));
-  int64_t total = 0;
-  for (int64_t t = T.leaf0; t < T.leaf0 + T.nleaf; ++t) {
-    int64_t len = 0;
-    for (int32_t k = ptr[t]; k < ptr[t + 1]; ++k) len += ls[src[k] + 1] - ls[src[k]];
-    total += len * (ls[t + 1] - ls[t]);
+  if (&S == &pl->lists[0]) {
+    int64_t total = 0;
+    for (int64_t t = T.leaf0; t < T.leaf0 + T.nleaf; ++t) {
+      int64_t len = 0;
+      for (int32_t k = ptr[t]; k < ptr[t + 1]; ++k) len += ls[src[k] + 1] - ls[src[k]];
+      total += len * (ls[t + 1] - ls[t]);
+    }
+    pl->p2p_inter = total;  // the same in both directions
   }
-  pl->p2p_inter = total;  // the same in both directions
   int64_t budget = kP2PItemMax;
   if (pl->prm.precision == FMM_FP64 && T.nleaf < kP2PLeaves)
-    budget = std::min(std::max(total / kP2PItems, kP2PItemMin), kP2PItemMax);
+    budget = std::min(std::max(pl->p2p_inter / kP2PItems, kP2PItemMin), kP2PItemMax);
   S.near = near_items(pl, T, ptr, src, ls, budget, st);
 }
 
-}  // namespace
-
-void make_work(fmm_plan* pl, int dir, hipStream_t st) {
+// Work distribution of direction dir.
+void make_direction(fmm_plan* pl, int dir, hipStream_t st) {
   ListSet& S = pl->lists[dir];
   std::vector<int32_t> mptr(pl->nbox + 1), ls(pl->nleaf + 1);
   FMM_HIP(hipMemcpyAsync(mptr.data(), S.m2l_ptr, sizeof(int32_t) * (pl->nbox + 1),
@@ -385,6 +394,22 @@ void make_work(fmm_plan* pl, int dir, hipStream_t st) {
   FMM_HIP(hipStreamSynchronize(st));
   make_items(pl, S, mptr, st);
   make_p2p_items(pl, S, tgt_side(pl, dir), ls, st);
+}
+
+}  // namespace
+
+void make_work(fmm_plan* pl, hipStream_t st) {
+  int64_t part = 0;
+  for (int d = 0; d < 2; ++d) {
+    make_direction(pl, d, st);
+    part = std::max(part, pl->lists[d].near.part_elems);
+  }
+  if (part == 0) return;
+  // partial rows: written and added within one pass, so that the two directions
+  // (whose passes a caller serialises) share them
+  const size_t es = pl->prm.precision == FMM_FP32 ? sizeof(float) : sizeof(double);
+  void* rows = plan_alloc(pl, es * (size_t)part);
+  for (int d = 0; d < 2; ++d) pl->lists[d].near.part = rows;
 }
 
 void build_lists(fmm_plan* pl, const TreeDesc& ts, const TreeDesc& tt, hipStream_t st) {

@@ -124,7 +124,7 @@ void build_union(fmm_plan* U, const std::vector<const fmm_plan*>& subs, hipStrea
   // mix targets of different problems
   U->side[0].npt = U->n;
   U->side[0].nleaf = U->nleaf;
-  for (int d = 0; d < 2; ++d) make_work(U, d, st);
+  make_work(U, st);
 }
 
 }  // namespace fmm

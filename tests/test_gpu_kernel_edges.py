@@ -202,3 +202,20 @@ def test_few_vectors_take_the_quicker_way(fmm, n, leaf, s, p, R, passes):
     u1, f1 = plan.evaluate(Q[R - 1])
     assert _rel(U[R - 1].double().cpu().numpy(), u1.double().cpu().numpy()) <= 1e-6
     assert _rel(Fd[R - 1].double().cpu().numpy(), f1.double().cpu().numpy()) <= 1e-6
+
+
+# both directions' partial rows of split direct lists lie in one buffer
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_split_lists_of_both_directions_share_their_rows(fmm, prec):
+    _say(f"[split lists] {prec} forward and transposed in turn")
+    pos, q = workloads.clustered(24000, 41)
+    dt = torch.float64 if prec == "fp64" else torch.float32
+    pt, qt = torch.from_numpy(pos).cuda(), torch.from_numpy(q).cuda().to(dt)
+    kw = dict(p=4, leaf_max=64, splits=2, theta=0.6, precision=prec)
+    plan = fmm.Plan(pt, **kw)
+    assert plan.info()["p2p_items"] > plan.info()["nleaf"]
+    forward = fmm.Plan(pt, **kw).evaluate(qt)
+    back = fmm.Plan(pt, **kw).evaluate_transposed(qt)
+    for _ in range(2):
+        for got, want in ((plan.evaluate(qt), forward), (plan.evaluate_transposed(qt), back)):
+            assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
