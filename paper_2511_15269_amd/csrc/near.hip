@@ -63,7 +63,7 @@ constexpr int kChunk = 8;
 // combined with cross-lane shuffles in a fixed order.
 template <typename T, bool FIELD, int G>
 __global__ __launch_bounds__(64) void k_p2p(
-    int64_t n, int item0, const int32_t* __restrict__ item_leaf,
+    int64_t n, const int32_t* __restrict__ item_leaf,
     const int32_t* __restrict__ item_kb, const int32_t* __restrict__ item_ke,
     const int64_t* __restrict__ item_out, const int32_t* __restrict__ leaf_start,
     const double* __restrict__ xs, const double* __restrict__ ys, const double* __restrict__ zs,
@@ -77,7 +77,7 @@ __global__ __launch_bounds__(64) void k_p2p(
   // neighbouring target leaves share most source leaves, so their records
   // stay in one XCD's L2, while leaves of unequal cost (several problems,
   // clustered points) spread over all XCDs
-  const int item = item0 + (int)xcd_chunked<64>(blockIdx.x, gridDim.x);
+  const int item = (int)xcd_chunked<64>(blockIdx.x, gridDim.x);
   const int leaf = item_leaf[item];
   const int lane = threadIdx.x;
   const int g = G == 1 ? 0 : lane / TL;
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(64) void k_p2p(
 // 75 -> 33 us with 256 threads an item.
 template <bool FIELD, int W>
 __global__ __launch_bounds__(W) __attribute__((amdgpu_waves_per_eu(4))) void k_p2p_wide(
-    int64_t n, int item0, const int32_t* __restrict__ item_leaf,
+    int64_t n, const int32_t* __restrict__ item_leaf,
     const int32_t* __restrict__ item_kb, const int32_t* __restrict__ item_ke,
     const int64_t* __restrict__ item_out, const int32_t* __restrict__ leaf_start,
     const double* __restrict__ xs, const double* __restrict__ ys, const double* __restrict__ zs,
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(W) __attribute__((amdgpu_waves_per_eu(4))) void k_p
   __shared__ T sums[2 * NC][W];
   __shared__ int ljs[W], lcnt[W];  // source leaves: first point, count
   __shared__ int lmax[W / 64], lself[W / 64];
-  const int item = item0 + (int)xcd_chunked<64>(blockIdx.x, gridDim.x);
+  const int item = (int)xcd_chunked<64>(blockIdx.x, gridDim.x);
   const int tid = threadIdx.x;
   const int leaf = item_leaf[item];
   const int st = leaf_start[leaf], nt = leaf_start[leaf + 1] - st;
@@ -363,7 +363,7 @@ __global__ __launch_bounds__(W) __attribute__((amdgpu_waves_per_eu(4))) void k_p
 // 13 us, uniform cube 2^20 (32 points a leaf) 0.59 -> 0.58 ms.
 template <bool FIELD, int W>
 __global__ __launch_bounds__(W) __attribute__((amdgpu_waves_per_eu(4))) void k_p2p_flat(
-    int64_t n, int item0, const int32_t* __restrict__ item_leaf,
+    int64_t n, const int32_t* __restrict__ item_leaf,
     const int32_t* __restrict__ item_kb, const int32_t* __restrict__ item_ke,
     const int64_t* __restrict__ item_out, const int32_t* __restrict__ leaf_start,
     const double* __restrict__ xs, const double* __restrict__ ys, const double* __restrict__ zs,
@@ -378,7 +378,7 @@ __global__ __launch_bounds__(W) __attribute__((amdgpu_waves_per_eu(4))) void k_p
   __shared__ int ljs[W], lcnt[W];  // source leaves: first point, count
   __shared__ int lpos[W + 1];          // points of the leaves before
   __shared__ int lmax[2], lself[2];
-  const int item = item0 + (int)xcd_chunked<64>(blockIdx.x, gridDim.x);
+  const int item = (int)xcd_chunked<64>(blockIdx.x, gridDim.x);
   const int tid = threadIdx.x;
   const int leaf = item_leaf[item];
   const int st = leaf_start[leaf], nt = leaf_start[leaf + 1] - st;
@@ -587,11 +587,12 @@ void run_near(fmm_plan* pl, const ListSet& Ls, const Src<T>* src, int64_t n, T* 
   const int runs = near_runs(pl, Ls, field, run);
   auto all = [&](const NearRun& r, auto field_tag) {
     constexpr bool F = decltype(field_tag)::value;
+    // (the run's items by pointer: with their offset as an argument k_p2p of two
+    // source groups took 158.7 instead of 154.3 us on 256 items of 17 points)
     auto launch = [&](auto kern, int threads) {
-      kern<<<(unsigned)r.count, threads, 0, sp>>>(n, (int)r.first, N.leaf, N.kb, N.ke, N.out,
-                                                  pl->leaf_start, pl->xs, pl->ys, pl->zs, src,
-                                                  Ls.p2p_src, pl->has_dup ? 1 : 0, near,
-                                                  (T*)N.part);
+      kern<<<(unsigned)r.count, threads, 0, sp>>>(
+          n, N.leaf + r.first, N.kb + r.first, N.ke + r.first, N.out + r.first, pl->leaf_start,
+          pl->xs, pl->ys, pl->zs, src, Ls.p2p_src, pl->has_dup ? 1 : 0, near, (T*)N.part);
     };
     if (r.form == kNearWave) {
       if (G == 1) launch(k_p2p<T, F, 1>, 64);
